@@ -124,6 +124,25 @@ kv_status check_cfg(const kv_model_cfg* c) {
   return KV_OK;
 }
 
+// The part of a pool's geometry that its configuration fixes.
+PoolGeom cfg_geom(const kv_model_cfg& c) {
+  PoolGeom g;
+  std::memset(&g, 0, sizeof(g));
+  g.block_elems = (int64_t)c.n_layers * 2 * c.n_kv_heads * c.block_size * c.head_dim;
+  g.max_blocks = (int32_t)ceil_div(c.max_pos, c.block_size);
+  g.L = c.n_layers;
+  g.Hq = c.n_q_heads;
+  g.Hkv = c.n_kv_heads;
+  g.dh = c.head_dim;
+  g.B = c.block_size;
+  g.d = c.d_model;
+  g.max_pos = c.max_pos;
+  g.b_shift = -1;
+  for (int sh = 0; sh < 7; ++sh)
+    if ((1 << sh) == c.block_size) g.b_shift = sh;
+  return g;
+}
+
 }  // namespace
 
 static_assert(sizeof(kv_model_cfg) == 56, "kv_model_cfg layout");
@@ -189,25 +208,14 @@ struct kv_pool {
   }
 
   PoolGeom geom() const {
-    PoolGeom g;
+    PoolGeom g = cfg_geom(cfg);
     g.pool = pool;
     g.tables = tables;
     g.rope_cos = rope_cos;
     g.rope_sin = rope_sin;
     g.rope_cos_g = rope_cos_g;
     g.rope_sin_g = rope_sin_g;
-    g.block_elems = (int64_t)cfg.n_layers * 2 * cfg.n_kv_heads * cfg.block_size * cfg.head_dim;
     g.max_blocks = max_blocks;
-    g.L = cfg.n_layers;
-    g.Hq = cfg.n_q_heads;
-    g.Hkv = cfg.n_kv_heads;
-    g.dh = cfg.head_dim;
-    g.B = cfg.block_size;
-    g.d = cfg.d_model;
-    g.max_pos = cfg.max_pos;
-    g.b_shift = -1;
-    for (int sh = 0; sh < 7; ++sh)
-      if ((1 << sh) == cfg.block_size) g.b_shift = sh;
     return g;
   }
   int64_t free_blocks() const { return tail - head; }
@@ -394,10 +402,9 @@ struct ScratchPlan {
 };
 
 // The wide form is taken where it leaves the layer groups as they are without it.
-ScratchPlan plan_scratch(const kv_pool* p, const AppendDesc& ad, size_t scratch_bytes) {
-  const kv_model_cfg& c = p->cfg;
+ScratchPlan plan_scratch(const kv_model_cfg& c, const AppendDesc& ad, size_t scratch_bytes) {
   const int64_t M = (int64_t)ad.batch * ad.T;
-  const PoolGeom g = p->geom();
+  const PoolGeom g = cfg_geom(c);
   auto plan = [&](AttnForm form) {
     ScratchPlan sp;
     sp.form = form;
@@ -421,7 +428,7 @@ ScratchPlan plan_scratch(const kv_pool* p, const AppendDesc& ad, size_t scratch_
 kv_status run_append(kv_pool* p, const AppendDesc& ad, const AllocArgs& aa, const void* x,
                      void* o, hipStream_t s, char* scratch, size_t scratch_bytes) {
   const kv_model_cfg& c = p->cfg;
-  const ScratchPlan sp = plan_scratch(p, ad, scratch_bytes);
+  const ScratchPlan sp = plan_scratch(c, ad, scratch_bytes);
   const int lc_max = sp.lc_max;
   if (lc_max < 1) return KV_ERR_BUFSIZE;
   KV_TRY(run_alloc(p, aa, s));
@@ -865,7 +872,7 @@ kv_status kv_materialize(kv_pool* p, const void* x_dev, int64_t T, int64_t pos0,
   if (nb > p->free_blocks()) return KV_ERR_OOM;
   const int64_t zero = 0;
   const AppendDesc ad = make_desc(1, &slot, &zero, &pos0, T);
-  if (plan_scratch(p, ad, p->scratch_bytes).lc_max < 1) return KV_ERR_BUFSIZE;
+  if (plan_scratch(p->cfg, ad, p->scratch_bytes).lc_max < 1) return KV_ERR_BUFSIZE;
   AllocArgs aa;
   std::memset(&aa, 0, sizeof(aa));
   aa.n_req = 1;
@@ -963,7 +970,7 @@ static kv_status attend_impl(kv_pool* p, const kv_state* states, int32_t batch,
   }
   if (need > p->free_blocks()) return KV_ERR_OOM;
   const AppendDesc ad = make_desc(batch, slots, nbef, pos0, T);
-  if (plan_scratch(p, ad, scratch_bytes).lc_max < 1) return KV_ERR_BUFSIZE;
+  if (plan_scratch(c, ad, scratch_bytes).lc_max < 1) return KV_ERR_BUFSIZE;
   const size_t elt = elt_bytes(c);
   KV_TRY(device_span(p->device, x_dev, (size_t)batch * T * c.d_model * elt));
   KV_TRY(device_span(p->device, o_dev,
@@ -1459,6 +1466,29 @@ kv_status kv_profile_launches(kv_pool* p, int32_t kind, float* out_ms, int64_t c
   const auto& v = p->launch_ms[kind];
   *n = (int64_t)v.size();
   for (int64_t i = 0; i < std::min<int64_t>(cap, *n); ++i) out_ms[i] = v[(size_t)i];
+  return KV_OK;
+}
+
+// For the tests, not part of the ABI (no device is needed): how an append of T
+// tokens to `batch` states, over at most max_keys keys with a work area of
+// scratch_bytes, would run.  out: layers per group (0: refused), bytes that
+// this takes, form (AttnForm), attention path (AttnPath), then for the
+// split-key path keys per chunk, chunks, lists, LDS bytes of the plan kernel.
+kv_status kvs_query_append(const kv_model_cfg* cfg, int32_t batch, int64_t T, int32_t max_keys,
+                           size_t scratch_bytes, int64_t* out) {
+  KV_TRY(check_cfg(cfg));
+  if (batch < 1 || batch > KV_MAX_BATCH || T < 1 || max_keys < T || !out) return KV_ERR_ARG;
+  AppendDesc ad;
+  std::memset(&ad, 0, sizeof(ad));
+  ad.batch = batch;
+  ad.T = (int32_t)T;
+  ad.max_keys = max_keys;
+  const ScratchPlan sp = plan_scratch(*cfg, ad, scratch_bytes);
+  std::fill(out, out + 8, 0);
+  out[0] = sp.lc_max;
+  out[1] = (int64_t)(sp.fixed + sp.lc_max * (sp.q_layer + sp.part_layer));
+  out[2] = sp.form;
+  out[3] = fast_attn_query(cfg_geom(*cfg), cfg->dtype, ad, sp.form, out + 4);
   return KV_OK;
 }
 

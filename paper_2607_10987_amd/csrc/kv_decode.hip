@@ -921,6 +921,14 @@ int64_t wide_keys(int64_t batch, int64_t vec) {
 int64_t wide_chunks(int64_t keys, int64_t ck) {
   return std::max<int64_t>(1, (keys + ck / 2) / ck);
 }
+// k_decode_plan holds a chunk's block ids of every member in LDS, beside 3080
+// bytes of its own in the 160 KiB of a CU: the bound on a chunk of many members
+// (64 of them, blocks of 16: 9984 keys).  The largest chunk that the fit asks
+// for is 2.5 times wide_keys, 10240 keys.
+constexpr size_t kPlanLds = 156 * 1024;
+size_t plan_lds(const PoolGeom& g, const AppendDesc& a, int64_t ck) {
+  return (size_t)a.batch * (ck / g.B) * sizeof(int);
+}
 DecodeForm decode_form(const PoolGeom& g, const AppendDesc& a, bool wide) {
   DecodeForm f;
   f.ck = a.batch == 1 ? kCK / 2 : kCK;
@@ -935,6 +943,7 @@ DecodeForm decode_form(const PoolGeom& g, const AppendDesc& a, bool wide) {
     int64_t ck = want;
     for (int64_t n = n0 + (n0 + 1) / 2; n >= std::max<int64_t>(1, 2 * n0 / 3); --n) {
       const int64_t c = std::max<int64_t>(((a.max_keys + n - 1) / n + unit - 1) / unit * unit, 256);
+      if (plan_lds(g, a, c) > kPlanLds) break;  // fewer chunks are larger still
       const int64_t nch = (a.max_keys + c - 1) / c;
       const int64_t rounds = (nch * U + slots - 1) / slots;
       const double fill = (double)(a.max_keys * U) / (double)(rounds * slots * c);
@@ -1001,6 +1010,14 @@ void decode_scratch(const PoolGeom& g, const AppendDesc& a, bool wide, size_t* p
            (f.split ? up256((size_t)f.nch * sizeof(uint64_t)) : 0);
 }
 
+void decode_query(const PoolGeom& g, const AppendDesc& a, bool wide, int64_t* out) {
+  const DecodeForm f = decode_form(g, a, wide);
+  out[0] = f.ck;
+  out[1] = f.nch;
+  out[2] = f.lists;
+  out[3] = (int64_t)plan_lds(g, a, f.ck);
+}
+
 size_t decode_scratch_bound(int64_t L, int64_t tokens, int64_t batch, int64_t Hq, int64_t Hkv,
                             int64_t max_keys) {
   size_t worst = 0;
@@ -1063,8 +1080,7 @@ hipError_t launch_decode_attn(const PoolGeom& g, const void* qbuf, const AppendD
   int* n_units = (int*)((char*)plan + unit_bytes(a, f));
   unsigned long long* late = (unsigned long long*)((char*)n_units + count_bytes(f));
   if (l0 == 0) {  // the grouping holds for every layer group of the call
-    const size_t dyn = (size_t)a.batch * (f.ck / g.B) * sizeof(int);
-    k_decode_plan<<<f.nch, kPlanThreads, dyn, s>>>(g, a, units, n_units, late, f);
+    k_decode_plan<<<f.nch, kPlanThreads, plan_lds(g, a, f.ck), s>>>(g, a, units, n_units, late, f);
   }
   const float sc = 1.4426950408889634f / sqrtf((float)kDh);
   int slots = std::min(f.nch * a.batch, 2 * f.nch + a.batch);

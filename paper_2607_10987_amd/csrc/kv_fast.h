@@ -25,6 +25,13 @@ void fast_scratch_need(const PoolGeom& g, int dtype, const AppendDesc& a, AttnFo
 // `max_keys` keys per state.
 size_t fast_scratch_bound(const kv_model_cfg& c, int64_t tokens, int32_t batch, int64_t max_keys);
 
+// How a call's attention runs in this form (for tests): its path, and for the
+// split-key path keys per chunk, chunks, lists and the plan kernel's dynamic LDS
+// bytes in out[0..3].
+enum AttnPath { kPathPortable = 0, kPathPrefill, kPathPacked, kPathSplitKey };
+AttnPath fast_attn_query(const PoolGeom& g, int dtype, const AppendDesc& a, AttnForm form,
+                         int64_t* out);
+
 hipError_t launch_qkv_fast(const PoolGeom& g, int dtype, const void* x, const void* w,
                            int64_t w_stride, const AppendDesc& a, void* qbuf, int l0, int lc,
                            hipStream_t s, bool* done);

@@ -8,6 +8,7 @@ void decode_scratch(const PoolGeom& g, const AppendDesc& a, bool wide, size_t* p
                     size_t* fixed);
 size_t decode_scratch_bound(int64_t L, int64_t tokens, int64_t batch, int64_t Hq, int64_t Hkv,
                             int64_t max_keys);
+void decode_query(const PoolGeom& g, const AppendDesc& a, bool wide, int64_t* out);
 hipError_t launch_decode_attn(const PoolGeom& g, const void* qbuf, const AppendDesc& a, bool wide,
                               void* part, void* plan, int lc, int l0, hipStream_t s);
 hipError_t launch_decode_merge(const PoolGeom& g, const AppendDesc& a, bool wide, void* o,
@@ -61,6 +62,16 @@ hipError_t launch_qkv_fast(const PoolGeom& g, int dtype, const void* x, const vo
 bool attn_mfma_ok(const PoolGeom& g, int dtype, const AppendDesc& a);
 hipError_t launch_attn_prefill(const PoolGeom& g, const void* qbuf, const AppendDesc& a, void* o,
                                int l0, int lc, hipStream_t s);
+
+AttnPath fast_attn_query(const PoolGeom& g, int dtype, const AppendDesc& a, AttnForm form,
+                         int64_t* out) {
+  if (takes_decode(g, dtype, a, form)) {
+    decode_query(g, a, form == kWide, out);
+    return kPathSplitKey;
+  }
+  if (!attn_mfma_ok(g, dtype, a)) return kPathPortable;
+  return form == kWide && attn_packed_ok(g, dtype, a) ? kPathPacked : kPathPrefill;
+}
 
 hipError_t launch_attn_fast(const PoolGeom& g, int dtype, const void* qbuf, const AppendDesc& a,
                             AttnForm form, void* o, void* part, void* plan, int l0, int lc,

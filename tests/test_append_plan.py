@@ -1,0 +1,64 @@
+"""How an append is cut up, over the whole range of calls (CPU: the library's
+own choice, asked without a device).
+
+The split-key attention fits its chunks to the call.  Whatever it picks, a
+chunk is whole blocks and whole stages of keys, the chunks cover the keys, the
+plan kernel's LDS (the block ids of every member's chunk, beside 3080 bytes of
+its own) fits in the 160 KiB of a CU, and the work area that kv_scratch_bytes
+asks for holds the call without cutting it into layer groups.
+"""
+import ctypes
+
+import pytest
+
+from paper_2607_10987_amd import kvstate as kv
+
+PORTABLE, PREFILL, PACKED, SPLIT = range(4)
+CU_LDS = 160 * 1024
+PLAN_STATIC = 3080
+
+
+def query(cfg, batch, T, keys, scratch):
+    out = (ctypes.c_int64 * 8)()
+    f = kv.lib().kvs_query_append
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_size_t,
+                  ctypes.c_void_p]
+    st = f(ctypes.byref(cfg), batch, T, keys, scratch, out)
+    assert st == 0, st
+    return dict(zip(("layers", "bytes", "form", "path", "ck", "nch", "lists", "lds"), out))
+
+
+def key_counts(top):
+    """Key counts up to `top`: the smallest, the edges of blocks and chunks,
+    and a spread whose step is not a divisor of any chunk size."""
+    ks = {1, 2, 15, 16, 17, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025}
+    n = 300
+    while n < top:
+        ks.add(n)
+        n += max(97, n // 37)
+    ks |= {m * 1024 + e for m in (2, 3, 4, 6, 8, 10, 16, 33) for e in (-1, 0, 1)}
+    ks |= {9983, 9984, 9985, 10048, 10200, 10239, 10240, 10241, top}
+    return sorted(k for k in ks if k <= top)
+
+
+@pytest.mark.parametrize("L,hq,hkv", [(32, 32, 8), (80, 64, 8), (28, 28, 4), (2, 32, 8),
+                                      (1, 4, 1), (40, 16, 16), (48, 48, 3), (16, 64, 4)])
+def test_split_key_plan_fits(L, hq, hkv):
+    for B in (16, 32, 64):
+        cfg = kv.make_cfg(L, 4096, hq, hkv, 128, B, "bf16", 140000, 64)
+        for T in (1, 2, 5, 32):
+            for batch in (1, 2, 3, 4, 7, 8, 13, 16, 17, 24, 31, 32, 33, 47, 62, 63, 64):
+                for keys in key_counts(140000 if batch < 4 else 40000):
+                    if keys < T:
+                        continue
+                    scratch = kv.kv_scratch_bytes(cfg, batch * T, batch, keys)
+                    q = query(cfg, batch, T, keys, scratch)
+                    what = (B, T, batch, keys, q)
+                    assert q["layers"] == L and q["bytes"] <= scratch, what
+                    if q["path"] != SPLIT:
+                        assert T > 1, what
+                        continue
+                    assert q["ck"] % 64 == 0 and q["ck"] % B == 0, what
+                    assert (q["nch"] - 1) * q["ck"] < keys <= q["nch"] * q["ck"], what
+                    assert q["lds"] >= batch * (q["ck"] // B) * 4, what
+                    assert q["lds"] + PLAN_STATIC <= CU_LDS, what

@@ -8,10 +8,14 @@ fork of a fork inside one chunk, members whose histories share nothing, key
 counts that end one key into a block, and units on both sides of the 32 query
 vectors that separate the two kernels.
 """
+import numpy as np
 import pytest
+import torch
 
 import synth
-from twin import Twin
+from oracle import apply_rope, attention_rows, project_q
+from paper_2607_10987_amd import kvstate as kv
+from twin import Twin, close, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -89,3 +93,46 @@ def test_packed_appends(gpu_available, n_ctx, agents, T):
     pair = tw.fork(other, 2)
     tw.attend(kids[:agents - 2] + pair, T)
     tw.close()
+
+
+def test_full_batch_over_one_large_chunk(gpu_available):
+    """64 agents x 4 query heads over 10111 keys, 32 layers of 8 KV heads: the
+    chunk that would hold all keys has more block ids (64 members x 640) than
+    the plan kernel's LDS takes.  Outputs of three members in the first and the
+    last layer against the float64 oracle's attention over the keys and values
+    that the device stored (tolerances of ``Twin``)."""
+    L, d, hq, hkv, dh, B, n_ctx, A = 32, 256, 32, 8, 128, 16, 10110, 64
+    cols, nb = (hq + 2 * hkv) * dh, -(-10110 // 16)
+    cfg = kv.make_cfg(L, d, hq, hkv, dh, B, "bf16", 10240, 70)
+    pool = kv.Pool(cfg, nb + A * 2 + 4, kv.kv_scratch_bytes(cfg, A, A, n_ctx + 2))
+    gen = torch.Generator(device="cuda").manual_seed(5)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    w = normal(L, cols, d) * d ** -0.5
+    pool.set_weights(w, cols * d)
+    h = kv.kv_pack_header()
+    h.magic, h.version, h.model_id, h.cfg = kv.KV_PACK_MAGIC, kv.KV_PACK_VERSION, cfg.model_id, cfg
+    h.n_tokens, h.n_blocks, h.block_bytes = n_ctx, nb, L * 2 * hkv * B * dh * 2
+    h.payload_bytes = nb * h.block_bytes
+    root = kv.kv_unpack(pool.h, h, normal(nb, L, 2, hkv, B, dh))
+    kids = kv.kv_fork(pool.h, root, A)
+    for step in range(2):                  # a private tail of one key, then of two
+        x = normal(A, d)
+        o = torch.empty((L, A, 1, hq * dh), dtype=torch.bfloat16, device="cuda")
+        kv.kv_attend(pool.h, kids, x, 1, o)
+        kv.kv_sync(pool.h)
+        assert torch.isfinite(o).all()
+        n = n_ctx + step + 1
+        pos = np.full(hq, n - 1)
+        for layer in (0, L - 1):
+            q = project_q(to_np(x), to_np(w[layer]), hq, hkv, dh)
+            for m in (0, 37, 63):
+                table = kv.kv_read_block_table(pool.h, kids[m])
+                t = pool.blocks_view()[table, layer].permute(1, 2, 0, 3, 4)
+                k, v = (to_np(u.reshape(hkv, -1, dh)[:, :n]) for u in t)
+                qr = apply_rope(q[m][:, None, :], np.full(1, n - 1), 10000.0)[:, 0, :]
+                want = attention_rows(qr, k, v, pos, np.arange(n), np.arange(hq) // (hq // hkv))
+                close(to_np(o[layer, m, 0]), want.reshape(-1), "bf16", f"layer {layer} agent {m}")
+    pool.close()
