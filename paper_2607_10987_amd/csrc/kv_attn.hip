@@ -57,7 +57,8 @@
 // the rows of several sequences (whole ones, as many as fill its token
 // groups).  The keys whose blocks all of them share (k_attn_shared finds how
 // many, in whole tiles) are read and scored once for all rows; then each
-// sequence's own keys, masked for the others' rows.  One workgroup per
+// sequence's own keys, masked for the others' rows, whose accumulators are left
+// alone (a value times p = 0 is not 0 if it is Inf or NaN).  One workgroup per
 // sequence left most of its rows empty and scored the shared keys once per
 // sequence: 6 agents x 29 tokens over 5003 keys (8B shape, 32 layers) 1163 us,
 // packed 580.  Sequences that share nothing cost the same number of tiles as
@@ -196,8 +197,7 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
   const int tq = t0 + tg * 32 + col;  // PACK: row of the pack
   const int n_seq = PACK ? min(per, a.batch - seq) : 1;
   const bool q_valid = tq < n_seq * a.T;
-  const int my_seq = PACK ? (q_valid ? seq + tq / a.T : -1) : seq;
-  const int uq = PACK ? (q_valid ? a.seq[my_seq].n_before + tq % a.T : 0) : sd.n_before + tq;
+  const int uq = sd.n_before + tq;  // last visible key (PACK: of the row's own sequence, below)
   const int key_end = PACK ? n_keys : min(n_keys, sd.n_before + t0 + QT);
   // PACK: tiles of the first sequence's keys (the first n_sh of them shared),
   // then those of the others' keys from n_sh * kKT on
@@ -275,16 +275,22 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
     if constexpr (PACK) {
       const uint32_t kl = lds0 + buf * kPTile * 2, vl = kl + kPS * kPTile * 2;
       const bool ragged = i_key + kKT > i_end;
+      // the lane's offsets, computed anew (held over the loop they spill)
+      int ln = (int)__lane_id();
+      settle(ln);
+      const int lr = ln >> 4, wr = wave * 4 + lr;
+      const uint32_t ko = (uint32_t)(((ln & 15) ^ kswz(wr)) * 16);
+      const uint32_t vo = (uint32_t)(((ln & 15) ^ vswz(wr)) * 16) + (uint32_t)kv_gap;
 #pragma unroll
       for (int jj = 0; jj < CJ; ++jj) {
         const int j = wave + jj * NW;
         const char* kb = pool_k + (uint64_t)(uint32_t)nid[jj] * blk_bytes;
-        // rows past the sequence's last key read that key (finite values)
-        int rb = ((j * 4) & (g.B - 1)) + (lane >> 4);
-        if (ragged) rb = min(i_key + j * 4 + (lane >> 4), i_end - 1) & (g.B - 1);
-        const uint32_t ro = (uint32_t)(rb - (lane >> 4)) * (kDh * 2);
-        lds_dma16_sv(kb, cko + ro, kl + j * 1024);
-        lds_dma16_sv(kb, cvo + ro, vl + j * 1024);
+        // rows past the sequence's last key read that key
+        int rb = ((j * 4) & (g.B - 1)) + lr;
+        if (ragged) rb = min(i_key + j * 4 + lr, i_end - 1) & (g.B - 1);
+        const uint32_t ro = (uint32_t)rb * (kDh * 2);
+        lds_dma16_sv(kb, ko + ro, kl + j * 1024);
+        lds_dma16_sv(kb, vo + ro, vl + j * 1024);
       }
       i_key += kKT;
       if (i_key >= i_end && i_seq + 1 < seq + n_seq) {
@@ -404,10 +410,23 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
   bool moved[HP];
   bf16x8 pf[HP][4];
   int m_seq = seq, m_key = n_sh * kKT, m_end = n_keys;  // PACK: the next masked tile
-  auto softmax = [&](floatx16 (*sc)[2], int tile, auto masked_c) {
+  // PACK, masked tiles: this lane's row is of the tile's sequence, and whether
+  // any row of the wave is / every valid row is
+  bool mine = true, any_mine = true, all_mine = true;
+  auto softmax = [&](floatx16 (*sc)[2], int tile, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
     const int k0 = PACK ? m_key : tile * kKT;
-    const int lim = PACK ? (my_seq == m_seq ? uq : -1) : uq;
+    int lim = uq;
+    if constexpr (PACK && MASKED) {
+      // row tq is token t of the tile's sequence, if of any (kept as arithmetic
+      // on scalars: registers held over the loop spill, and a reload waits for
+      // the copies in flight)
+      const int t = t0 + tg * 32 + (int)__lane_id() % 32 - (m_seq - seq) * a.T;
+      mine = t >= 0 && t < a.T;
+      any_mine = __ballot(mine) != 0;
+      all_mine = __ballot(!mine && t < (seq + n_seq - m_seq) * a.T) == 0;
+      lim = mine ? m_end - a.T + t : -1;
+    }
 #pragma unroll
     for (int hh = 0; hh < HP; ++hh) {
       if constexpr (MASKED) {
@@ -481,20 +500,44 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
     }
   };
   // O^T += V^T P^T for keys [16 s_lo, 16 s_hi) of the tile in stage sb, V^T
-  // operands by transposed LDS reads, each feeding the products of all HP heads
-  auto pv = [&](int sb, int s_lo, int s_hi) {
+  // operands by transposed LDS reads, each feeding the products of all HP heads.
+  // PACK: a masked tile must leave the rows of other sequences alone, not only
+  // add p = 0 times its values (0 * Inf and 0 * NaN are NaN), so a wave without
+  // rows of the tile's sequence skips the products and one with some of them
+  // keeps the other columns.
+  auto pv = [&](int sb, int s_lo, int s_hi, auto masked_c) __attribute__((always_inline)) {
+    constexpr bool SELECT = PACK && decltype(masked_c)::value;
     const uint32_t vb = sb * kPTile * 2;
+    auto v_op = [&](int mt, int s4) {
+      const uint32_t so = vb + s4 * 16 * kDh * 2;
+      const v4s vv[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16(KV_LDS4(vof[mt * 2] + so)),
+                         __builtin_amdgcn_ds_read_tr16_b64_v4i16(KV_LDS4(vof[mt * 2 + 1] + so))};
+      return __builtin_bit_cast(bf16x8, vv);
+    };
+    if constexpr (SELECT) {
+      if (!any_mine) return;
+      if (!all_mine) {
+        if (s_hi < 4) return;  // all of them after the barrier
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int hh = 0; hh < HP; ++hh) {
+            floatx16 t = oacc[hh][mt];
+#pragma unroll
+            for (int s4 = 0; s4 < 4; ++s4)
+              t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_op(mt, s4), pf[hh][s4], t, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) oacc[hh][mt][e] = mine ? t[e] : oacc[hh][mt][e];
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        return;
+      }
+    }
 #pragma unroll
     for (int s4 = s_lo; s4 < s_hi; ++s4) {
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        const uint32_t so = vb + s4 * 16 * kDh * 2;
-        const v4s r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            KV_LDS4(vof[mt * 2] + so));
-        const v4s r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            KV_LDS4(vof[mt * 2 + 1] + so));
-        const v4s vv[2] = {r0, r1};
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, vv);
+        const bf16x8 vf = v_op(mt, s4);
 #pragma unroll
         for (int hh = 0; hh < HP; ++hh)
           oacc[hh][mt] =
@@ -516,11 +559,12 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
   // buffer of tile - 1.  Steps run in pairs that swap the two score sets, so
   // no scores are copied between registers.  sb = the stage of tile.
   floatx16 sB[HP][2];
-  auto step = [&](int tile, int sb, floatx16 (*scur)[2], floatx16 (*snx)[2], auto masked_c) {
+  auto step = [&](int tile, int sb, floatx16 (*scur)[2], floatx16 (*snx)[2],
+                  auto masked_c) __attribute__((always_inline)) {
     qk((sb + 1) % kPS, snx);
     softmax(scur, tile, masked_c);
     finish();
-    pv(sb, 0, 2);
+    pv(sb, 0, 2, masked_c);
     if (tile + 2 < n_tiles) {
       // copies of one wave complete in order, 2 CJ per tile: tile + 2 is the
       // newest issued.  Every read of the buffer about to be refilled (tile
@@ -529,7 +573,7 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
       barrier_only();
       if (tile + kPS - 1 < n_tiles) issue(tile + kPS - 1, (sb + kPS - 1) % kPS);
     }
-    pv(sb, 2, 4);
+    pv(sb, 2, 4, masked_c);
   };
   // a step left over after the pairs: its next scores become sacc
   auto step_copy = [&](int tile, auto masked_c) {
@@ -565,7 +609,7 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
   if (tile < lim) step_copy(tile++, std::true_type{});
   softmax(sacc, tile, std::true_type{});
   finish();
-  pv(tile % kPS, 0, 4);
+  pv(tile % kPS, 0, 4, std::true_type{});
 
   float l_tot[HP];
 #pragma unroll
