@@ -61,9 +61,11 @@
 // alone (a value times p = 0 is not 0 if it is Inf or NaN).  One workgroup per
 // sequence left most of its rows empty and scored the shared keys once per
 // sequence: 6 agents x 29 tokens over 5003 keys (8B shape, 32 layers) 1163 us,
-// packed 580.  Sequences that share nothing cost the same number of tiles as
-// in workgroups of their own.  Block ids come through scalar loads here (a
-// pack's tables together can exceed the LDS).
+// packed 540.  Sequences that share too little for that (k_attn_shared) get
+// workgroups of their own in the same launch: packed, four of the 70B shape with
+// nothing in common take three rounds of four sequences against ten of one.
+// Block ids come through scalar loads here (a pack's tables together can
+// exceed the LDS).
 #include <algorithm>
 #include <type_traits>
 
@@ -140,9 +142,16 @@ typedef const __attribute__((address_space(4))) int32_t cint;
 
 // grid (packs), block 256: shared[p] = keys, a multiple of kKT, that are
 // cached for every sequence of pack p (sequences p * per .. + per - 1) in the
-// same blocks.  Latency-bound, once per call.
+// same blocks; -1 where the pack's sequences are better off in workgroups of
+// their own, which depends on what they share.  Packed, a workgroup takes the
+// shared tiles once and 1.3 times the private ones (masked, with a select after
+// the products: 6 x 16 tokens over 5003 private keys 1560 us packed, 1050 each
+// for itself), and where workgroups are few the device's rounds of them fit the
+// larger ones less well (fit = rounds packed x sequences per pack, over rounds of
+// single ones).
+// Latency-bound, once per call.
 __global__ void __launch_bounds__(256)
-k_attn_shared(PoolGeom g, AppendDesc a, int per, int32_t* __restrict__ shared) {
+k_attn_shared(PoolGeom g, AppendDesc a, int per, float fit, int32_t* __restrict__ shared) {
   __shared__ int s_min;
   const int s0 = blockIdx.x * per, s1 = min(s0 + per, a.batch);
   if (threadIdx.x == 0) {
@@ -162,12 +171,20 @@ k_attn_shared(PoolGeom g, AppendDesc a, int per, int32_t* __restrict__ shared) {
   __syncthreads();
   atomicMin(&s_min, first << g.b_shift);
   __syncthreads();
-  if (threadIdx.x == 0) shared[blockIdx.x] = s_min & ~(kKT - 1);
+  if (threadIdx.x == 0) {
+    const int n_sh = s_min / kKT;
+    int tiles = 0;
+    for (int s = s0; s < s1; ++s) tiles += (a.seq[s].n_before + a.T + kKT - 1) / kKT;
+    const float packed = n_sh + 1.3f * (tiles - (s1 - s0) * n_sh);
+    shared[blockIdx.x] = packed * fit <= tiles ? n_sh * kKT : -1;
+  }
 }
 
-// grid (batch x query tiles x Hkv x lc, flattened; PACK: packs x Hkv x lc),
-// block 64 * (8 / HP): each wavefront computes HP query heads of one group of
-// 32 tokens.  per, shared: PACK only.
+// grid (batch x query tiles x Hkv x lc, flattened; PACK: the packs, then the
+// sequences that are not the first of theirs, each x Hkv x lc; the latter have
+// nothing to do where the pack is taken as one), block 64 * (8 / HP): each
+// wavefront computes HP query heads of one group of 32 tokens.  per, shared:
+// PACK only.
 template <int G, int HP, bool PACK>
 __global__ void __launch_bounds__(64 * (kPW / HP), 1)
 k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
@@ -184,10 +201,18 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
   const int hl = lane >> 5, col = lane & 31;
   const int tg = wave / (G / HP), hw = wave % (G / HP);
   const int qt_per_seq = PACK ? 1 : (a.T + QT - 1) / QT;
-  const int nx = PACK ? (a.batch + per - 1) / per : a.batch * qt_per_seq;
-  const int lid = xcd_remap(blockIdx.x, gridDim.x);
+  const int packs = PACK ? (a.batch + per - 1) / per : 0;
+  const int n_lead = PACK ? (int)(gridDim.x / a.batch) * packs : (int)gridDim.x;
+  const bool lead = !PACK || (int)blockIdx.x < n_lead;
+  const int nx = !PACK ? a.batch * qt_per_seq : lead ? packs : a.batch - packs;
+  const int lid = lead ? xcd_remap(blockIdx.x, n_lead)
+                       : xcd_remap(blockIdx.x - n_lead, gridDim.x - n_lead);
   const int bx = lid % nx, gk = (lid / nx) % g.Hkv, lc = lid / (nx * g.Hkv);
-  const int seq = PACK ? bx * per : bx / qt_per_seq;  // PACK: the first of the pack's
+  const int pack = !PACK ? 0 : lead ? bx : bx / (per - 1);
+  const int keys_sh = PACK ? ((cint*)shared)[pack] : 0;
+  if (PACK && !lead && keys_sh >= 0) return;
+  // PACK: the first of the workgroup's sequences
+  const int seq = PACK ? pack * per + (lead ? 0 : 1 + bx % (per - 1)) : bx / qt_per_seq;
   const int qt = qt_per_seq - 1 - (bx % qt_per_seq);  // long tiles first
   const int l = l0 + lc;
   const int M = a.batch * a.T;
@@ -195,13 +220,13 @@ k_attn_pipe(PoolGeom g, const uint16_t* __restrict__ qbuf, AppendDesc a,
   const int n_keys = sd.n_before + a.T;
   const int t0 = qt * QT;
   const int tq = t0 + tg * 32 + col;  // PACK: row of the pack
-  const int n_seq = PACK ? min(per, a.batch - seq) : 1;
+  const int n_seq = PACK && keys_sh >= 0 ? min(per, a.batch - seq) : 1;
   const bool q_valid = tq < n_seq * a.T;
   const int uq = sd.n_before + tq;  // last visible key (PACK: of the row's own sequence, below)
   const int key_end = PACK ? n_keys : min(n_keys, sd.n_before + t0 + QT);
-  // PACK: tiles of the first sequence's keys (the first n_sh of them shared),
-  // then those of the others' keys from n_sh * kKT on
-  const int n_sh = PACK ? ((cint*)shared)[bx] / kKT : 0;
+  // PACK: tiles of the first sequence's keys (the first n_sh of them visible to
+  // every row), then those of the others' keys from n_sh * kKT on
+  const int n_sh = !PACK ? 0 : (keys_sh >= 0 ? keys_sh : sd.n_before) / kKT;
   int n_tiles = (key_end + kKT - 1) / kKT;
   if (PACK)
     for (int i = 1; i < n_seq; ++i)
@@ -675,10 +700,14 @@ hipError_t launch_attn_packed(const PoolGeom& g, const void* qbuf, const AppendD
   const int G = g.Hq / g.Hkv, per = pack_size(g, a), packs = (a.batch + per - 1) / per;
   const float sc = 1.4426950408889634f / sqrtf((float)kDh);
   int32_t* shared = (int32_t*)plan;
-  if (l0 == 0) k_attn_shared<<<packs, 256, 0, s>>>(g, a, per, shared);
+  if (l0 == 0) {
+    auto rounds = [&](int n) { return (float)(((int64_t)n * g.Hkv * lc + 255) / 256); };
+    const float fit = rounds(packs) * a.batch / (rounds(a.batch) * packs);
+    k_attn_shared<<<packs, 256, 0, s>>>(g, a, per, fit, shared);
+  }
   constexpr int HP = kHeadsPerWave;
   auto kernel = G == 4 ? k_attn_pipe<4, HP, true> : k_attn_pipe<8, HP, true>;
-  kernel<<<(unsigned)(packs * g.Hkv * lc), 64 * (kPW / HP), 0, s>>>(
+  kernel<<<(unsigned)(a.batch * g.Hkv * lc), 64 * (kPW / HP), 0, s>>>(
       g, (const uint16_t*)qbuf, a, (uint16_t*)o, l0, sc, per, shared);
   return hipGetLastError();
 }

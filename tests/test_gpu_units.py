@@ -95,6 +95,24 @@ def test_packed_appends(gpu_available, n_ctx, agents, T):
     tw.close()
 
 
+@pytest.mark.parametrize("hq,T", [(32, 20), (64, 9)])
+def test_packed_appends_that_share_little(gpu_available, hq, T):
+    """Packs are decided one by one: three forks of one context are taken as
+    one, members of unrelated contexts (63 to 411 keys, the last one alone in
+    its pack) in workgroups of their own of the same launch, and so are forks
+    whose private part outweighs the common one."""
+    shape = synth.ModelShape("8b-s", 16, 512, hq, 8, 128, 16, "bf16")
+    tw = Twin(shape, n_blocks=400, max_pos=700, max_states=40, wl="little", check_kv=False)
+    roots = [context(tw, n, 20 + i) for i, n in enumerate((411, 63, 64, 200, 130))]
+    forks = tw.fork(roots[0], 3)
+    tw.attend(forks + roots[1:], T)                  # 3 | 3 | 1 at either T
+    tw.attend(roots[1:] + forks, T)                  # no pack shares anything but the last
+    short = tw.fork(roots[1], 4)
+    tw.attend(short, 130)                            # 130 private keys after 63 common ones
+    tw.attend(short + forks, T)
+    tw.close()
+
+
 def test_full_batch_over_one_large_chunk(gpu_available):
     """64 agents x 4 query heads over 10111 keys, 32 layers of 8 KV heads: the
     chunk that would hold all keys has more block ids (64 members x 640) than
