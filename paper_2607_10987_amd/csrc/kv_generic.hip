@@ -21,6 +21,7 @@
 // -> 68 us, attention 1006 -> 123 us in all, against one workgroup per 32
 // rows x head staged through LDS and one wavefront per (row, head).
 #include <algorithm>
+#include <type_traits>
 
 #include "kv_internal.h"
 
@@ -196,6 +197,7 @@ k_attn_generic(PoolGeom g, const T* __restrict__ qbuf, AppendDesc a, T* __restri
   const int v = min(vt * 16 + lr, vecs - 1);
   const int t = v / G, nkeys = sd.n_before + t + 1;
   const int n_all = sd.n_before + min(vt * 16 + 15, vecs - 1) / G + 1;  // keys of the tile's last
+  const int n_first = sd.n_before + vt * 16 / G + 1;  // and of its first: seen by every vector
   const T* q = qbuf + (((int64_t)lc * M + sq * a.T + t) * g.Hq + hk * G + v % G) * dh;
   floatx4 qf[NC], oacc[NC];
 #pragma unroll
@@ -207,15 +209,32 @@ k_attn_generic(PoolGeom g, const T* __restrict__ qbuf, AppendDesc a, T* __restri
   const int32_t* trow = g.tables + (int64_t)sd.slot * g.max_blocks;
   const int64_t kbase = tile_off(g, l, 0, hk, 0), vbase = tile_off(g, l, 1, hk, 0);
   float m = -INFINITY, lsum = 0.f;
-  for (int k0 = wave * 16; k0 < n_all; k0 += 16 * NW) {
-    // the tile's keys past the last read that one (masked, finite)
-    const int key = min(k0 + lr, n_all - 1), kb = key / g.B, slot = key - kb * g.B;
+  // one tile of 16 keys; MASKED: some vector does not see all of them, and those
+  // past the last read that one
+  auto tile = [&](int k0, auto masked_c) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    const int key = MASKED ? min(k0 + lr, n_all - 1) : k0 + lr, kb = key / g.B, slot = key - kb * g.B;
     const int32_t blk = trow[kb];
     const T* kp = pool + (int64_t)blk * g.block_elems + kbase + (int64_t)slot * dh + 4 * lg;
     floatx4 kf[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c)
       if (c < nc) kf[c] = ld4<true>(kp + c * 16, 4);
+    // 0 * Inf and 0 * NaN are NaN: values that are not finite are kept from the
+    // vectors that do not see their key (read as the keys are, beside them)
+    bool odd = false;
+    if constexpr (MASKED) {
+      const T* ve = kp + (vbase - kbase);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        if (c < nc) {
+          const floatx4 f = ld4<true>(ve + c * 16, 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            odd |= (__float_as_uint(f[e]) & 0x7f800000u) == 0x7f800000u;
+        }
+      odd = __any(odd);
+    }
     const T* vp[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -234,7 +253,7 @@ k_attn_generic(PoolGeom g, const T* __restrict__ qbuf, AppendDesc a, T* __restri
     float p[4], mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = k0 + 4 * lg + r < nkeys ? sc[r] * scale : -INFINITY;
+      p[r] = !MASKED || k0 + 4 * lg + r < nkeys ? sc[r] * scale : -INFINITY;
       mx = fmaxf(mx, p[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
@@ -253,15 +272,37 @@ k_attn_generic(PoolGeom g, const T* __restrict__ qbuf, AppendDesc a, T* __restri
     lsum = lsum * alpha + ps;
     m = mn;
 #pragma unroll
+    for (int c = 0; c < NC; ++c) oacc[c] *= alpha;
+    if (MASKED && odd) {
+      // a key at a time, into the columns that see it
+#pragma unroll 1
+      for (int i = 0; i < 16 && k0 + i < n_all; ++i) {
+        const int r = i & 3;
+        const bool own = lg == i >> 2, seen = k0 + i < nkeys;
+        const T* vi = r == 0 ? vp[0] : r == 1 ? vp[1] : r == 2 ? vp[2] : vp[3];
+        const float pi = own ? (r == 0 ? p[0] : r == 1 ? p[1] : r == 2 ? p[2] : p[3]) : 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (c < nc) {
+            const floatx4 t = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                own ? ld<T>(vi + c * 16) : 0.f, pi, oacc[c], 0, 0, 0);
+            if (seen) oacc[c] = t;
+          }
+      }
+      return;
+    }
+#pragma unroll
     for (int c = 0; c < NC; ++c)
       if (c < nc) {
-        oacc[c] *= alpha;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           oacc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ld<T>(vp[r] + c * 16), p[r], oacc[c], 0,
                                                          0, 0);
       }
-  }
+  };
+  int k0 = wave * 16;
+  for (; k0 + 16 <= n_first; k0 += 16 * NW) tile(k0, std::false_type{});
+  for (; k0 < n_all; k0 += 16 * NW) tile(k0, std::true_type{});
   // combine the wavefronts: [NW][16][dh + 4] outputs, then m and l [NW][16]
   const int ldo = dh + 4;
   float* s_m = sm + NW * 16 * ldo;

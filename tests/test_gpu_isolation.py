@@ -82,3 +82,48 @@ def test_agents_are_isolated(gpu_available, L, hq, hkv, n_ctx, agents, T, what):
     same = torch.equal(a[:, rest], b[:, rest])
     assert same, what
     p.pool.close()
+
+
+@pytest.mark.parametrize("hq,hkv,dh,dt", [(4, 2, 64, "f32"), (3, 1, 48, "f32"), (2, 2, 256, "f32"),
+                                          (5, 1, 64, "bf16"), (3, 3, 112, "bf16")])
+@pytest.mark.parametrize("n_before,T,at", [(0, 20, 9), (5, 33, 32), (200, 7, 3), (300, 1, 0)])
+def test_later_tokens_do_not_reach_earlier_ones(gpu_available, hq, hkv, dh, dt, n_before, T, at):
+    """The portable attention: token `at` has infinite values (and finite
+    queries and keys: input channel 0 feeds only the values).  Tokens before it
+    keep their outputs, those from it on are infinite.  Up to the order of
+    sums, which may differ in the tile of keys that holds the values: float32
+    arithmetic within 2e-5, one bf16 rounding of it within 2^-8 of the value."""
+    L, d, B = 2, 64, 16
+    q, dtype, cols = hq * dh, TORCH[dt], (hq + 2 * hkv) * dh
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    w = (torch.randn(L, cols, d, generator=gen, device="cuda") * d ** -0.5).to(dtype)
+    w[:, :, 0] = 0
+    w[:, (hq + hkv) * dh:, 0] = 16
+    cfg = kv.make_cfg(L, d, hq, hkv, dh, B, dt, 400, 4)
+    pool = kv.Pool(cfg, 64, kv.kv_scratch_bytes(cfg, 400, 1, 400))
+    pool.set_weights(w, cols * d)
+    x0 = torch.randn(max(n_before, 1), d, generator=gen, device="cuda").to(dtype)
+    x = torch.randn(1, T, d, generator=gen, device="cuda").to(dtype)
+    x0[:, 0] = x[:, :, 0] = 0
+    bad = x.clone()
+    bad[0, at, 0] = 3e38
+
+    def outputs(xi):
+        if n_before == 0:
+            o = torch.empty((L, T, q), dtype=dtype, device="cuda")
+            kv.kv_release(pool.h, kv.kv_materialize(pool.h, xi, T, 0, o))
+            return o
+        o0 = torch.empty((L, n_before, q), dtype=dtype, device="cuda")
+        s = kv.kv_materialize(pool.h, x0, n_before, 0, o0)
+        o = torch.empty((L, 1, T, q), dtype=dtype, device="cuda")
+        kv.kv_attend(pool.h, [s], xi, T, o)
+        kv.kv_release(pool.h, s)
+        return o[:, 0]
+
+    a, b = outputs(x).double(), outputs(bad).double()
+    assert bool(torch.isfinite(a).all())
+    assert bool((b[:, at:] == float("inf")).all())
+    err = (a[:, :at] - b[:, :at]).abs()
+    bound = 2e-5 + (2.0 ** -8 * a[:, :at].abs() if dt == "bf16" else 0.0)
+    assert bool((err <= bound).all()), float(err.max())
+    pool.close()
