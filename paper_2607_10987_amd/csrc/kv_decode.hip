@@ -46,6 +46,8 @@
 
 namespace kvs {
 
+bool attn_mfma_ok(const PoolGeom& g, int dtype, const AppendDesc& a);
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -986,10 +988,14 @@ bool decode_mfma_ok(const PoolGeom& g, int dtype, const AppendDesc& a) {
         g.b_shift >= 0 && (a.batch == 1 ? kCK / 2 : kCK) % g.B == 0))
     return false;
   if (a.T == 1) return true;
+  // Appends: in the place of the prefill attention only, which rounds its
+  // probabilities to bf16 as well.  What that does not cover (other head groups,
+  // longer block tables) keeps the portable kernel's float32 ones.
+  if (!attn_mfma_ok(g, dtype, a)) return false;
   const int G = g.Hq / g.Hkv;
   const DecodeForm f = decode_form(g, a, true);
   if ((int64_t)a.batch * a.T * G > kMaxVecAppend || f.lists > kPersMaxChunks) return false;
-  // The prefill attention (G = 4 or 8) runs a round of 256 workgroups per 256
+  // The prefill attention runs a round of 256 workgroups per 256
   // (sequence, KV head, layer), each 11 us and 1 us per 32 keys; this path
   // costs three launches, about 40 us, and the keys at about 5.5 TB/s.  8B
   // shape: a prefill of 16 tokens 12 against 31 us, 8 tokens over 5003 keys 207
@@ -997,7 +1003,7 @@ bool decode_mfma_ok(const PoolGeom& g, int dtype, const AppendDesc& a) {
   const double items = (double)a.batch * g.Hkv * g.L;
   const double rounds = ceil(items / 256);
   const double split = 40 + (double)a.max_keys * g.Hkv * g.L * 512 / 5.5e6;
-  return (G != 4 && G != 8) || split < rounds * (11 + a.max_keys / 32.0);
+  return split < rounds * (11 + a.max_keys / 32.0);
 }
 
 // Scratch of a call: the split-key partials of one layer, [M][Hq][lists][kPart]

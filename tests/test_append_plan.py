@@ -62,3 +62,22 @@ def test_split_key_plan_fits(L, hq, hkv):
                     assert (q["nch"] - 1) * q["ck"] < keys <= q["nch"] * q["ck"], what
                     assert q["lds"] >= batch * (q["ck"] // B) * 4, what
                     assert q["lds"] + PLAN_STATIC <= CU_LDS, what
+
+
+@pytest.mark.parametrize("hq,hkv,keys,T,batch,path", [
+    (32, 8, 8000, 4, 2, SPLIT), (64, 8, 8000, 4, 2, SPLIT),      # 4 and 8 query heads
+    (32, 8, 8000, 64, 1, PREFILL), (32, 8, 8000, 16, 8, PACKED),
+    (8, 8, 8000, 4, 2, PORTABLE), (16, 8, 8000, 4, 2, PORTABLE),
+    (24, 8, 8000, 4, 2, PORTABLE), (48, 8, 8000, 2, 1, PORTABLE),
+    (64, 4, 8000, 8, 1, PORTABLE), (24, 8, 8000, 64, 1, PORTABLE),
+    (32, 8, 131072, 4, 2, SPLIT), (32, 8, 131073, 4, 2, PORTABLE),   # block tables above 32 KiB
+    (24, 8, 8000, 1, 2, SPLIT), (32, 8, 139990, 1, 2, SPLIT),        # decode: any head group
+])
+def test_appends_keep_float32_probabilities(hq, hkv, keys, T, batch, path):
+    """The split-key attention rounds probabilities to bf16, as the prefill
+    attention does.  It takes appends from that one only: head groups and table
+    sizes that run in the portable kernel (float32 throughout) stay there at
+    every number of query vectors."""
+    cfg = kv.make_cfg(32, 4096, hq, hkv, 128, 16, "bf16", 140000, 64)
+    q = query(cfg, batch, T, keys, kv.kv_scratch_bytes(cfg, batch * T, batch, keys))
+    assert q["path"] == path, q

@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     (2, 100, 2, 2, 128, 16, "f32", 128, 1, 65),
     (1, 96, 6, 2, 144, 3, "bf16", 40, 3, 7),
     (1, 70, 3, 3, 256, 64, "f32", 65, 2, 15),
+    (2, 256, 6, 2, 128, 16, "bf16", 300, 3, 7),   # three query heads per KV head
     (40, 36, 4, 2, 32, 4, "f32", 97, 2, 33),
     (40, 34, 4, 2, 32, 4, "bf16", 66, 3, 40),
 ])
