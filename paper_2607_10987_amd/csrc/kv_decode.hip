@@ -914,9 +914,10 @@ constexpr int kMaxVecAppend = 128;
 // chunks is the one whose (chunk, layer, KV head) items best fill whole rounds
 // of the workgroups that are resident for this many vectors, 5 (one
 // wavefront), 4 (one, two query tiles), 2 (four) or 1 (eight) per CU, with a
-// chunk costing its keys, its partials and about 32 keys to start.  A batch of
-// one has no shared blocks and its chunks are its only parallelism: about
-// 512 (+5-10% against 1024).
+// chunk costing its keys, its partials and about 32 keys to start.  (Rounds of
+// the whole call: in a work area that cuts it into layer groups they are
+// smaller.)  A batch of one has no shared blocks and its chunks are its only
+// parallelism: about 512 (+5-10% against 1024).
 int64_t wide_keys(int64_t batch, int64_t vec) {
   return std::max<int64_t>(batch == 1 ? kCK / 2 : kCK, std::min<int64_t>(16 * vec, 4 * kCK));
 }
@@ -936,14 +937,29 @@ DecodeForm decode_form(const PoolGeom& g, const AppendDesc& a, bool wide) {
   f.ck = a.batch == 1 ? kCK / 2 : kCK;
   const int64_t G = g.Hq / g.Hkv, vec = (int64_t)a.batch * a.T * G;
   if (wide) {
-    const int64_t per_cu = vec <= 32 ? 5 : vec <= 64 ? 4 : vec <= 128 ? 2 : 1;
-    const int64_t slots = 256 * per_cu, U = (int64_t)g.L * g.Hkv;
+    // One token of one state: all units are alike.  While 1024-key chunks need
+    // at most two rounds of four workgroups per CU, the fit is to those (a fifth
+    // resident one only takes bandwidth from the others) and may go down to 256
+    // keys (few layers) or up to 1024: over five shapes of 16 to 640 (layer, KV
+    // head) pairs and 20 key counts to 34816, 1.6% above the best of ten fixed
+    // sizes on average, against 7% for 384 keys, 10% for 512.  Beyond two rounds
+    // units drift apart and full rounds do not count: 384 keys up to four of them
+    // (8B shape, 9000 keys, 4 steps: 811 us against 947 for three full rounds of
+    // 768), then the fit below, near 512 (70B shape, 8000 keys, a step: 438
+    // against 449 for 384).  Where the pool lies in memory moves these times by
+    // up to 4%.
+    const int64_t U = (int64_t)g.L * g.Hkv;
+    const double kilo = (double)a.max_keys * U / (kCK * 1024.0);  // rounds of 1024-key units
+    const bool one = a.batch == 1 && a.T == 1, few = one && kilo <= 2;
+    const int64_t per_cu = few ? 4 : vec <= 32 ? 5 : vec <= 64 ? 4 : vec <= 128 ? 2 : 1;
+    const int64_t slots = 256 * per_cu;
     const int64_t want = wide_keys(a.batch, vec);
     const int64_t unit = std::max(64, g.B);
     const int64_t n0 = wide_chunks(a.max_keys, want);
     double best = 0;
     int64_t ck = want;
-    for (int64_t n = n0 + (n0 + 1) / 2; n >= std::max<int64_t>(1, 2 * n0 / 3); --n) {
+    const int64_t n_lo = std::max<int64_t>(1, few ? n0 / 2 : 2 * n0 / 3);
+    for (int64_t n = few ? 2 * n0 : n0 + (n0 + 1) / 2; n >= n_lo; --n) {
       const int64_t c = std::max<int64_t>(((a.max_keys + n - 1) / n + unit - 1) / unit * unit, 256);
       if (plan_lds(g, a, c) > kPlanLds) break;  // fewer chunks are larger still
       const int64_t nch = (a.max_keys + c - 1) / c;
@@ -955,12 +971,7 @@ DecodeForm decode_form(const PoolGeom& g, const AppendDesc& a, bool wide) {
         ck = c;
       }
     }
-    f.ck = (int)ck;
-    // one token of one state: its equal units overlap from round to round, so
-    // filling few rounds exactly only lengthens them (4 steps, 8B shape, fitted
-    // against 384 keys: 1300 keys 179 / 155 us, 3000 323 / 289, 6007 552 / 526,
-    // 12000 1049 / 1016; from there on alike)
-    if (a.batch == 1 && a.T == 1 && a.max_keys < 16 * kCK && 384 % g.B == 0) f.ck = 384;
+    f.ck = one && !few && kilo < 4 ? 384 : (int)ck;
   }
   f.nch = (a.max_keys + f.ck - 1) / f.ck;
   f.split = wide && a.batch > 1 ? 1 : 0;
@@ -1042,7 +1053,8 @@ size_t decode_scratch_bound(int64_t L, int64_t tokens, int64_t batch, int64_t Hq
   for (int64_t rows = 1; rows <= most; ++rows)
     for (const int64_t b : {(int64_t)1, std::min(batch, rows)}) {
       const int64_t ck = wide_keys(b, rows * G), n0 = wide_chunks(max_keys, ck);
-      add(rows, b, b > 1 ? 2 * (n0 + (n0 + 1) / 2) : n0 + (n0 + 1) / 2 + 1, 2 * ck);
+      const int64_t n = rows == 1 ? 2 * n0 : n0 + (n0 + 1) / 2;
+      add(rows, b, b > 1 ? 2 * n : n + 1, 2 * ck);
     }
   return worst;
 }

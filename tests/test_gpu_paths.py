@@ -230,10 +230,9 @@ def test_compose_bf16_head_dim_96(gpu_available):
 def test_decode_many_chunks(gpu_available):
     """Decode over a 139990-token context (a seeded payload unpacked into the
     pool; one KV head of 128 channels, so the oracle stays small): a batch of
-    one cuts it into 274 chunks of 512 keys, more than the persistent kernel
-    indexes, so the per-unit stream kernel runs; batches of 2 and 3 forked
-    agents cut it into 137 chunks of 1024 keys, which the persistent kernel
-    finds through its unit counts in three registers per lane."""
+    one in 438 chunks of 320 keys (two layers need many to fill the GPU),
+    batches of 2 and 3 forked agents in 199 of 704 keys with two lists of units
+    each; the merge reads a query's partials in several rounds."""
     shape = synth.ModelShape("long", 2, 256, 4, 1, 128, 16, "bf16")
     n_ctx = 139990
     nb = -(-n_ctx // shape.block_size)
