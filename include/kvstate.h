@@ -141,9 +141,13 @@ kv_status kv_pool_bytes(const kv_model_cfg* cfg, int64_t n_blocks, size_t* pool_
                         size_t* meta_bytes);
 
 /* Scratch bytes that let a single materialize/attend call of `tokens` total
- * new tokens (batch * T) over at most `max_keys` keys per state run with all
- * layers at once.  A smaller scratch area works: layers are then processed
- * in groups (at least one layer must fit). */
+ * new tokens (batch * T), of up to `batch` states, over at most `max_keys` keys
+ * per state run with all layers at once and in the fastest form there is for
+ * it.  A smaller scratch area works: decode and short appends then use a form
+ * that takes less (agents share the keys of whole 1024-key chunks only, about
+ * two thirds of the bytes), and layers are processed in groups (at least one
+ * layer must fit).  Which form ran may show in the last bits of an output
+ * (sums end at other keys).  Host arithmetic of up to some tens of ms. */
 size_t kv_scratch_bytes(const kv_model_cfg* cfg, int64_t tokens, int32_t batch,
                         int64_t max_keys);
 
@@ -238,14 +242,17 @@ kv_status kv_attend(kv_pool* pool, const kv_state* states, int32_t batch, const 
  * operation and kernels, with its work area in a fixed device array of
  * KV_NOALLOC_SCRATCH_MB MiB that the library holds on each GPU until the
  * process ends, instead of the pool's scratch area (the pool may have none).
+ * (Where the two areas differ in what fits, so may the form of the attention,
+ * and with it the last bits of the output: see kv_scratch_bytes.)
  * Calls no allocating routine on the host or the device.  The call runs in
  * layer groups that fit the array: per layer, the query rows
  * (batch * T * Hq * dh elements) and, for decode (T = 1), the split-key
  * partials (batch * Hq * ceil(max keys / chunk) * (dh + 4) floats, chunks of
  * 1024 keys, 512 for a batch of one), plus the decode plan once; a call of
- * which not even one layer fits is KV_ERR_BUFSIZE and changes nothing.  Where
- * it costs no layers per group, a faster form with up to twice the partials
- * runs (also for short appends).
+ * which not even one layer fits is KV_ERR_BUFSIZE and changes nothing.  That
+ * is the least a call takes.  Where it costs no layers per group, a faster form
+ * runs, also for short appends (T > 1): two lists of partials per chunk for
+ * more than one state, chunks of 256 keys and more fitted to the call.
  * Nothing in the array needs to start at zero.  Every call on one GPU uses
  * that GPU's array, so calls that overlap on one GPU (several pools or
  * streams, several host threads) race: the caller orders them.

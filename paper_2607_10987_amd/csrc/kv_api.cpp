@@ -735,7 +735,7 @@ size_t kv_scratch_bytes(const kv_model_cfg* cfg, int64_t tokens, int32_t batch,
   if (check_cfg(cfg) != KV_OK || tokens < 1 || batch < 1) return 0;
   const size_t q = (size_t)cfg->n_layers * tokens * cfg->n_q_heads * cfg->head_dim *
                    elt_bytes(*cfg);
-  return align256(q) + fast_scratch_bound(*cfg, tokens, batch, max_keys);
+  return align256(q) + fast_scratch_bound(cfg_geom(*cfg), cfg->dtype, tokens, batch, max_keys);
 }
 
 kv_status kv_pool_create(const kv_model_cfg* cfg, int64_t n_blocks, void* pool_dev,

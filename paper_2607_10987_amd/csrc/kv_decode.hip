@@ -1035,27 +1035,52 @@ void decode_query(const PoolGeom& g, const AppendDesc& a, bool wide, int64_t* ou
   out[3] = (int64_t)plan_lds(g, a, f.ck);
 }
 
-size_t decode_scratch_bound(int64_t L, int64_t tokens, int64_t batch, int64_t Hq, int64_t Hkv,
+// The most that any call of up to `batch` states, `tokens` new tokens in all and
+// max_keys keys takes.  The smallest layout has a formula; the wide form is
+// asked for each (batch, T): its choice only changes where a multiple of 64 keys
+// or a half step of wide_chunks is passed, so both ends of every 64 keys cover
+// all key counts.  A few ms; the formula with the most chunks that decode_form
+// considers is twice as much scratch (8B shape, 16 agents, 33792 keys: 866 MB
+// against 416; the smallest layout takes 285).
+size_t decode_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int64_t batch,
                             int64_t max_keys) {
-  size_t worst = 0;
-  auto add = [&](int64_t rows, int64_t b, int64_t lists, int64_t ck) {
-    worst = std::max(worst, (size_t)L * (rows * Hq * lists * kPart * sizeof(float) + 256) +
-                                (size_t)lists * b * (kUnitHdr + ck / 16) * sizeof(int32_t) +
-                                (size_t)lists * (2 * sizeof(int) + sizeof(uint64_t)) + 4 * 256);
+  const int64_t L = g.L, Hq = g.Hq, G = g.Hq / g.Hkv;
+  auto total = [&](int64_t rows, int64_t b, int64_t lists, int64_t ck) {
+    return (size_t)L * (rows * Hq * lists * kPart * sizeof(float) + 256) +
+           (size_t)lists * b * (kUnitHdr + ck / 16) * sizeof(int32_t) +
+           (size_t)lists * (2 * sizeof(int) + sizeof(uint64_t)) + 4 * 256;
   };
   auto chunks = [&](int64_t ck) { return (max_keys + ck - 1) / ck; };
-  // T = 1 calls of any batch up to `batch` in the smallest layout
-  add(1, 1, chunks(kCK / 2), kCK / 2);
-  add(batch, batch, chunks(kCK), kCK);
-  // the wide form for any number of rows, with the most chunks decode_form takes
-  const int64_t G = Hq / Hkv;
-  const int64_t most = std::max(batch, std::min(tokens, (int64_t)kMaxVecAppend / G));
-  for (int64_t rows = 1; rows <= most; ++rows)
-    for (const int64_t b : {(int64_t)1, std::min(batch, rows)}) {
-      const int64_t ck = wide_keys(b, rows * G), n0 = wide_chunks(max_keys, ck);
-      const int64_t n = rows == 1 ? 2 * n0 : n0 + (n0 + 1) / 2;
-      add(rows, b, b > 1 ? 2 * n : n + 1, 2 * ck);
+  size_t worst = std::max(total(1, 1, chunks(kCK / 2), kCK / 2),
+                          total(batch, batch, chunks(kCK), kCK));
+  AppendDesc a = {};
+  auto wide = [&](int64_t b, int64_t T) {
+    a.batch = (int32_t)b;
+    a.T = (int32_t)T;
+    const int64_t want = wide_keys(b, b * T * G);
+    for (int64_t hi = (max_keys + 63) / 64 * 64; hi > 0; hi -= 64) {
+      const int64_t n = 2 * wide_chunks(hi, want) + 1;  // at least as many as decode_form takes
+      if (total(b * T, b, b > 1 ? 2 * n : n, 3 * want) <= worst) return;
+      const int64_t at[2] = {std::max(T, hi - 63), std::min(max_keys, hi)};
+      if (at[0] > at[1]) continue;
+      bool any = false;
+      for (const int64_t keys : at) {
+        a.max_keys = (int32_t)keys;
+        any |= decode_mfma_ok(g, dtype, a);
+      }
+      for (const int64_t keys : at) {
+        if (!any) break;
+        a.max_keys = (int32_t)keys;
+        size_t per = 0, fixed = 0;
+        decode_scratch(g, a, true, &per, &fixed);
+        worst = std::max(worst, L * per + fixed);
+      }
     }
+  };
+  const int64_t most = std::min<int64_t>(batch, KV_MAX_BATCH);
+  for (int64_t b = most; b >= 1; --b) wide(b, 1);
+  for (int64_t b = 1; b <= most; ++b)
+    for (int64_t T = std::min(tokens, (int64_t)kMaxVecAppend / G) / b; T > 1; --T) wide(b, T);
   return worst;
 }
 

@@ -23,7 +23,8 @@ void fast_scratch_need(const PoolGeom& g, int dtype, const AppendDesc& a, AttnFo
                        size_t* per_layer, size_t* fixed);
 // An upper bound of the same for calls of `tokens` new tokens over at most
 // `max_keys` keys per state.
-size_t fast_scratch_bound(const kv_model_cfg& c, int64_t tokens, int32_t batch, int64_t max_keys);
+size_t fast_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int32_t batch,
+                          int64_t max_keys);
 
 // How a call's attention runs in this form (for tests): its path, and for the
 // split-key path keys per chunk, chunks, lists and the plan kernel's dynamic LDS

@@ -6,7 +6,7 @@ namespace kvs {
 bool decode_mfma_ok(const PoolGeom& g, int dtype, const AppendDesc& a);
 void decode_scratch(const PoolGeom& g, const AppendDesc& a, bool wide, size_t* per_layer,
                     size_t* fixed);
-size_t decode_scratch_bound(int64_t L, int64_t tokens, int64_t batch, int64_t Hq, int64_t Hkv,
+size_t decode_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int64_t batch,
                             int64_t max_keys);
 void decode_query(const PoolGeom& g, const AppendDesc& a, bool wide, int64_t* out);
 hipError_t launch_decode_attn(const PoolGeom& g, const void* qbuf, const AppendDesc& a, bool wide,
@@ -40,10 +40,10 @@ void fast_scratch_need(const PoolGeom& g, int dtype, const AppendDesc& a, AttnFo
     *fixed = attn_packed_bytes(g, a);
 }
 
-size_t fast_scratch_bound(const kv_model_cfg& c, int64_t tokens, int32_t batch,
+size_t fast_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int32_t batch,
                           int64_t max_keys) {
-  // split-key partials and the work-unit plan of a decode call
-  return decode_scratch_bound(c.n_layers, tokens, batch, c.n_q_heads, c.n_kv_heads, max_keys);
+  // split-key partials and the work-unit plan (more than a packed call's counts)
+  return decode_scratch_bound(g, dtype, tokens, batch, max_keys);
 }
 
 bool qkv_mfma_ok(const PoolGeom& g, int dtype);

@@ -2,10 +2,11 @@
 own choice, asked without a device).
 
 The split-key attention fits its chunks to the call.  Whatever it picks, a
-chunk is whole blocks and whole stages of keys, the chunks cover the keys, the
-plan kernel's LDS (the block ids of every member's chunk, beside 3080 bytes of
-its own) fits in the 160 KiB of a CU, and the work area that kv_scratch_bytes
-asks for holds the call without cutting it into layer groups.
+chunk is whole blocks and whole stages of keys, the chunks cover the keys, and
+the plan kernel's LDS (the block ids of every member's chunk, beside 3080 bytes
+of its own) fits in the 160 KiB of a CU.  The work area that kv_scratch_bytes
+asks for holds every call that it is asked for in its fastest form, without
+cutting it into layer groups.
 """
 import ctypes
 
@@ -51,10 +52,9 @@ def test_split_key_plan_fits(L, hq, hkv):
                 for keys in key_counts(140000 if batch < 4 else 40000):
                     if keys < T:
                         continue
-                    scratch = kv.kv_scratch_bytes(cfg, batch * T, batch, keys)
-                    q = query(cfg, batch, T, keys, scratch)
+                    q = query(cfg, batch, T, keys, 1 << 44)
                     what = (B, T, batch, keys, q)
-                    assert q["layers"] == L and q["bytes"] <= scratch, what
+                    assert q["layers"] == L, what
                     if q["path"] != SPLIT:
                         assert T > 1, what
                         continue
@@ -62,6 +62,34 @@ def test_split_key_plan_fits(L, hq, hkv):
                     assert (q["nch"] - 1) * q["ck"] < keys <= q["nch"] * q["ck"], what
                     assert q["lds"] >= batch * (q["ck"] // B) * 4, what
                     assert q["lds"] + PLAN_STATIC <= CU_LDS, what
+
+
+def q_bytes(cfg, rows):
+    return -(-rows * cfg.n_q_heads * cfg.head_dim * 2 // 256) * 256 * cfg.n_layers
+
+
+@pytest.mark.parametrize("L,hq,hkv,B,batch,tokens,keys,factor", [
+    (32, 32, 8, 16, 16, 16, 33792, 1.5), (80, 64, 8, 32, 4, 4, 16388, 1.7),
+    (32, 32, 8, 16, 64, 64, 33792, 1.05), (32, 32, 8, 16, 32, 200, 6015, 1.05),
+    (2, 32, 8, 16, 5, 40, 9001, 11), (28, 28, 4, 64, 7, 7, 20011, 2.1),
+])
+def test_work_area_holds_every_smaller_call(L, hq, hkv, B, batch, tokens, keys, factor):
+    """A work area of kv_scratch_bytes runs every call of at most as many
+    states, tokens and keys in the form that it would take in an unlimited one,
+    in one layer group, and is at most `factor` times what the least layout takes
+    to decode the whole batch (1024-key chunks; two layers over several tokens
+    take many more chunks to fill the GPU)."""
+    cfg = kv.make_cfg(L, 4096, hq, hkv, 128, B, "bf16", keys + 8, 64)
+    area = kv.kv_scratch_bytes(cfg, tokens, batch, keys)
+    for b in sorted({1, 2, 3, 5, batch // 3, batch // 2 + 1, batch - 1, batch} - {0}):
+        for T in sorted({1, 2, 3, 5, 12, 31, 32, tokens // b}):
+            if T * b > tokens or b > batch:
+                continue
+            for k in {*range(T, keys, max(61, keys // 90)), *range(max(T, keys - 70), keys + 1)}:
+                want, got = query(cfg, b, T, k, 1 << 44), query(cfg, b, T, k, area)
+                assert got == want and got["layers"] == L, (b, T, k, want, got)
+    least = L * batch * hq * -(-keys // 1024) * 132 * 4
+    assert area - q_bytes(cfg, tokens) <= factor * least + (1 << 20), (area, least)
 
 
 @pytest.mark.parametrize("hq,hkv,keys,T,batch,path", [
