@@ -1492,4 +1492,20 @@ kv_status kvs_query_append(const kv_model_cfg* cfg, int32_t batch, int64_t T, in
   return KV_OK;
 }
 
+// The same for the projection of M token rows and lc layers on n_cu CUs.  out:
+// kernel (QkvPick::Kernel, -1: portable), token rows per tile, weight stages.
+kv_status kvs_query_projection(const kv_model_cfg* cfg, int32_t M, int32_t lc, int32_t n_cu,
+                               int32_t* out) {
+  KV_TRY(check_cfg(cfg));
+  if (M < 1 || lc < 1 || n_cu < 1 || !out) return KV_ERR_ARG;
+  const PoolGeom g = cfg_geom(*cfg);
+  QkvPick p = {QkvPick::kTiles, 0, 0};
+  const bool ok = qkv_mfma_ok(g, cfg->dtype);
+  if (ok) p = pick_qkv(g, M, lc, n_cu);
+  out[0] = ok ? (int32_t)p.kernel : -1;
+  out[1] = p.rows;
+  out[2] = p.stages;
+  return KV_OK;
+}
+
 }  // extern "C"

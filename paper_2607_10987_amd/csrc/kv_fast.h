@@ -26,6 +26,15 @@ void fast_scratch_need(const PoolGeom& g, int dtype, const AppendDesc& a, AttnFo
 size_t fast_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int32_t batch,
                           int64_t max_keys);
 
+// The bf16 projection of M token rows and lc layers on a device of n_cu CUs:
+// its kernel, token rows per tile and stages of the weights (kTiles).
+struct QkvPick {
+  enum Kernel { kStream, kRowsLds, kRows, kTile32, kTiles } kernel;
+  int rows, stages;
+};
+bool qkv_mfma_ok(const PoolGeom& g, int dtype);
+QkvPick pick_qkv(const PoolGeom& g, int M, int lc, int n_cu);
+
 // How a call's attention runs in this form (for tests): its path, and for the
 // split-key path keys per chunk, chunks, lists and the plan kernel's dynamic LDS
 // bytes in out[0..3].

@@ -46,7 +46,6 @@ size_t fast_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int32_t 
   return decode_scratch_bound(g, dtype, tokens, batch, max_keys);
 }
 
-bool qkv_mfma_ok(const PoolGeom& g, int dtype);
 hipError_t launch_qkv_mfma(const PoolGeom& g, const void* x, const void* w, int64_t w_stride,
                            const AppendDesc& a, void* qbuf, int l0, int lc, hipStream_t s);
 

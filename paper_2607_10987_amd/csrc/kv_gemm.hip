@@ -284,9 +284,10 @@ k_qkv_mfma(PoolGeom g, const uint16_t* __restrict__ x, const uint16_t* __restric
 // Prefill projection, main loop with direct global->LDS loads
 // (global_load_lds_dwordx4: lane i of a wavefront writes LDS bytes
 // [16 i, 16 i + 16) of the instruction's 1 KiB destination) and a 2- or 3-stage
-// pipeline of K-steps of 64, with no register staging.  Tile 256 channels x
-// 256 tokens, 8 wavefronts of 128 channels x 64 tokens (a wave owns a head's
-// rotation pairs, so RoPE stays in registers).  LDS rows are 128 bytes (64 k); the
+// pipeline of K-steps of 64, with no register staging.  Tile 256 channels x BT
+// (128, 192 or 256) tokens; 8 wavefronts of 128 channels x 64 tokens (BT = 256)
+// or 64 channels x BT / 2 (a wave owns its channels' rotation partners, so RoPE
+// stays in registers).  LDS rows are 128 bytes (64 k); the
 // 16-byte chunk q of row r is stored at chunk slot q ^ f(r), f(r) =
 // (r >> 1) & 7, so that the 16 consecutive rows an operand read serves in one
 // LDS cycle (16 lanes x 16 bytes over 64 banks) cover the 16 bank groups.
@@ -1013,91 +1014,118 @@ hipError_t cu_count(int* n) {
 }
 }  // namespace
 
+namespace {
+// Token rows of a column chunk of k_qkv_decode_pst: the whole row, else halves, ...
+int pst_cols(const PoolGeom& g, int M) {
+  int kx = g.d;
+  while ((size_t)M * kx * 2 > kPstX && kx % (2 * kDmaKB * 32) == 0) kx /= 2;
+  return kx;
+}
+// and of k_qkv_decode_lds: the whole row if two workgroups still fit in a
+// CU's LDS, else halves, quarters, ... (multiples of the batch width)
+constexpr size_t kCfBytes = 16 * (kDh + 4) * 4;
+int lds_cols(const PoolGeom& g, int M) {
+  int kc = g.d;
+  while (kc % (2 * 32 * kDecU) == 0 && (size_t)M * (kc + 8) * 2 + kCfBytes > 80 * 1024) kc /= 2;
+  return kc;
+}
+}  // namespace
+
+QkvPick pick_qkv(const PoolGeom& g, int M, int lc, int n_cu) {
+  const int kx = pst_cols(g, M);
+  if (M <= kPstRows && g.d % (kDmaKB * 32) == 0 && kx % (kDmaKB * 32) == 0 &&
+      (size_t)M * kx * 2 <= kPstX)
+    return {QkvPick::kStream, M <= 16 ? 16 : M <= 32 ? 32 : 64, 0};
+  if (M <= 16 && g.d % (32 * kDecU) == 0 &&
+      (size_t)M * (lds_cols(g, M) + 8) * 2 + kCfBytes <= 160 * 1024)
+    return {QkvPick::kRowsLds, 16, 0};
+  if (M <= 32 && g.d % 512 == 0) return {QkvPick::kRows, M <= 16 ? 16 : 32, 0};
+  if (M <= 32) return {QkvPick::kTile32, 32, 0};
+  // qkv_mfma_ok: d % kDlBK == 0.  The token tile whose rounds of CUs cost least,
+  // in the measured ratio of their times (8B / 70B shapes, 32 / 80 layers: 333
+  // rows 548 us as 2 x 192 against 592 as 3 x 128 and 620 as 2 x 256, 300 rows
+  // of the 70B shape 4.25 ms against 4.76 and 5.13; 768 rows 943 us as 3 x 256
+  // against 993 as 4 x 192).  256-token tiles keep a third weight stage in calls
+  // of one token tile and of up to 32 rounds (512 rows 640 against 707 us, 2048
+  // rows 2.42 against 2.50 ms).  In longer calls it still takes fewer cycles (8192
+  // rows of the 8B shape, same order of copies: 130.0 against 134.8 million),
+  // but workgroups drift apart, the L2 hit rate falls from 73 to 31%, 74 GB
+  // instead of 27 come from beyond the L2 and the clock drops from 1.50 to 1.35
+  // GHz: 11.6 against 11.0 ms (4096 rows 5.61 against 5.40).
+  auto rounds = [&](int bt) {
+    const int64_t heads = (g.Hq + 2 * g.Hkv) / 2;  // pairs: 256 channels
+    return (heads * ((M + bt - 1) / bt) * lc + n_cu - 1) / n_cu;
+  };
+  const double c128 = rounds(128) * 0.62, c192 = rounds(192) * 0.82, c256 = rounds(256);
+  if (c256 <= c128 && c256 <= c192)
+    return {QkvPick::kTiles, 256, M <= 256 || rounds(256) <= 32 ? 3 : 2};
+  return {QkvPick::kTiles, c128 <= c192 ? 128 : 192, 3};
+}
+
 hipError_t launch_qkv_mfma(const PoolGeom& g, const void* x, const void* w, int64_t w_stride,
                            const AppendDesc& a, void* qbuf, int l0, int lc, hipStream_t s) {
   const int M = a.batch * a.T;
   const int N = (g.Hq + 2 * g.Hkv) * kDh;
-  // x staged in column chunks of kc: the whole row if two workgroups still
-  // fit in a CU's LDS, else halves, quarters, ... (multiples of the batch width)
-  int kc = g.d;
-  const size_t cf_bytes = 16 * (kDh + 4) * 4;
-  while (kc % (2 * 32 * kDecU) == 0 && (size_t)M * (kc + 8) * 2 + cf_bytes > 80 * 1024) kc /= 2;
-  const size_t x_lds = (size_t)M * (kc + 8) * 2;
-  // token-row chunk of the tile-group kernel: the whole row, else halves, ...
-  int kx = g.d;
-  while ((size_t)M * kx * 2 > kPstX && kx % (2 * kDmaKB * 32) == 0) kx /= 2;
-  if (M <= kPstRows && g.d % (kDmaKB * 32) == 0 && kx % (kDmaKB * 32) == 0 &&
-      (size_t)M * kx * 2 <= kPstX) {
-    int n_cu = 0;
-    if (cu_count(&n_cu) != hipSuccess) return hipErrorInvalidDevice;
-    // tiles per workgroup: the most (up to kPstTiles) whose grid wastes at
-    // most 3% of its last round of CUs, else the least wasteful
-    const int tiles = (g.Hq + 2 * g.Hkv) * lc;
-    int tpw = 1;
-    double best = 2.0;
-    for (int t = kPstTiles; t >= 1; --t) {
-      const int64_t grid = (tiles + t - 1) / t;
-      const int64_t rounds = (grid + n_cu - 1) / n_cu;
-      const double waste = (double)(rounds * n_cu - grid) / (double)(rounds * n_cu);
-      if (waste <= 0.03) {
-        tpw = t;
-        break;
+  const uint16_t *xp = (const uint16_t*)x, *wp = (const uint16_t*)w;
+  uint16_t* qp = (uint16_t*)qbuf;
+  int n_cu = 0;
+  if (cu_count(&n_cu) != hipSuccess) return hipErrorInvalidDevice;
+  const QkvPick pick = pick_qkv(g, M, lc, n_cu);
+  switch (pick.kernel) {
+    case QkvPick::kStream: {
+      // tiles per workgroup: the most (up to kPstTiles) whose grid wastes at
+      // most 3% of its last round of CUs, else the least wasteful
+      const int tiles = (g.Hq + 2 * g.Hkv) * lc;
+      int tpw = 1;
+      double best = 2.0;
+      for (int t = kPstTiles; t >= 1; --t) {
+        const int64_t grid = (tiles + t - 1) / t;
+        const int64_t rounds = (grid + n_cu - 1) / n_cu;
+        const double waste = (double)(rounds * n_cu - grid) / (double)(rounds * n_cu);
+        if (waste <= 0.03) {
+          tpw = t;
+          break;
+        }
+        if (waste < best) {
+          best = waste;
+          tpw = t;
+        }
       }
-      if (waste < best) {
-        best = waste;
-        tpw = t;
-      }
+      const int kx = pst_cols(g, M);
+      auto kernel = pick.rows == 16   ? k_qkv_decode_pst<1>
+                    : pick.rows == 32 ? k_qkv_decode_pst<2>
+                                      : k_qkv_decode_pst<4>;
+      kernel<<<(tiles + tpw - 1) / tpw, 64 * kDecWaves, (size_t)M * kx * 2, s>>>(
+          g, xp, wp, w_stride, a, qp, l0, lc, tpw, kx);
+      break;
     }
-    auto kernel = M <= 16 ? k_qkv_decode_pst<1> : M <= 32 ? k_qkv_decode_pst<2> : k_qkv_decode_pst<4>;
-    kernel<<<(tiles + tpw - 1) / tpw, 64 * kDecWaves, (size_t)M * kx * 2, s>>>(
-        g, (const uint16_t*)x, (const uint16_t*)w, w_stride, a, (uint16_t*)qbuf, l0, lc, tpw, kx);
-  } else if (M <= 16 && g.d % (32 * kDecU) == 0 && x_lds + cf_bytes <= 160 * 1024) {
-    dim3 grid(N / kDh, 1, lc);
-    k_qkv_decode_lds<<<grid, 64 * kDecWaves, x_lds, s>>>(g, (const uint16_t*)x, (const uint16_t*)w,
-                                                         w_stride, a, (uint16_t*)qbuf, l0, kc);
-  } else if (M <= 16 && g.d % 512 == 0) {
-    dim3 grid(N / kDh, 1, lc);
-    k_qkv_decode<1><<<grid, 64 * kDecWaves, 0, s>>>(g, (const uint16_t*)x, (const uint16_t*)w,
-                                                   w_stride, a, (uint16_t*)qbuf, l0);
-  } else if (M <= 32 && g.d % 512 == 0) {
-    dim3 grid(N / kDh, 1, lc);
-    k_qkv_decode<2><<<grid, 64 * kDecWaves, 0, s>>>(g, (const uint16_t*)x, (const uint16_t*)w,
-                                                   w_stride, a, (uint16_t*)qbuf, l0);
-  } else if (M <= 32) {
-    dim3 grid(N / 128, 1, lc);
-    k_qkv_mfma<128, 32, 4, 1><<<grid, kThreads, 0, s>>>(g, (const uint16_t*)x, (const uint16_t*)w,
-                                                        w_stride, a, (uint16_t*)qbuf, l0);
-  } else {  // qkv_mfma_ok: d % kDlBK == 0
-    // The token tile whose rounds of CUs cost least, in the measured ratio of
-    // their times (8B / 70B shapes, 32 / 80 layers: 333 rows 548 us as 2 x 192
-    // against 592 as 3 x 128 and 620 as 2 x 256, 300 rows of the 70B shape 4.25
-    // ms against 4.76 and 5.13; 768 rows 943 us as 3 x 256 against 993 as 4 x
-    // 192).  256-token tiles keep a third weight stage in calls of up to 32
-    // rounds (512 rows 640 against 707 us, 2048 rows 2.42 against 2.50 ms; 4096
-    // rows 5.10 against 4.96, 8192 rows 10.4 against 9.8 ms: measured, the
-    // cause of the loss in long calls is not known).
-    int n_cu = 0;
-    if (cu_count(&n_cu) != hipSuccess) return hipErrorInvalidDevice;
-    auto rounds = [&](int bt) {
-      const int64_t tiles = (int64_t)(N / 256) * ((M + bt - 1) / bt) * lc;
-      return (tiles + n_cu - 1) / n_cu;
-    };
-    const double c128 = rounds(128) * 0.62, c192 = rounds(192) * 0.82, c256 = rounds(256);
-    auto run = [&](auto one, auto many, int bt) {
-      const int ty = (M + bt - 1) / bt;
-      auto kernel = ty == 1 ? one : many;
-      kernel<<<dim3(N / 256, ty, lc), kDlThreads, 0, s>>>(
-          g, (const uint16_t*)x, (const uint16_t*)w, w_stride, a, (uint16_t*)qbuf, l0);
-    };
-    if (c256 <= c128 && c256 <= c192) {
-      if (rounds(256) <= 32)
-        run(k_qkv_dl<256, 2, 3, 2, false, true>, k_qkv_dl<256, 2, 3, 2, false, false>, 256);
-      else
-        run(k_qkv_dl<256, 2, 2, 2, true, true>, k_qkv_dl<256, 2, 2, 2, true, false>, 256);
-    } else if (c128 <= c192) {
-      run(k_qkv_dl<128, 4, 3, 3, false, true>, k_qkv_dl<128, 4, 3, 3, false, false>, 128);
-    } else {
-      run(k_qkv_dl<192, 4, 3, 2, false, true>, k_qkv_dl<192, 4, 3, 2, false, false>, 192);
+    case QkvPick::kRowsLds: {
+      const int kc = lds_cols(g, M);
+      k_qkv_decode_lds<<<dim3(N / kDh, 1, lc), 64 * kDecWaves, (size_t)M * (kc + 8) * 2, s>>>(
+          g, xp, wp, w_stride, a, qp, l0, kc);
+      break;
+    }
+    case QkvPick::kRows: {
+      auto kernel = pick.rows == 16 ? k_qkv_decode<1> : k_qkv_decode<2>;
+      kernel<<<dim3(N / kDh, 1, lc), 64 * kDecWaves, 0, s>>>(g, xp, wp, w_stride, a, qp, l0);
+      break;
+    }
+    case QkvPick::kTile32:
+      k_qkv_mfma<128, 32, 4, 1><<<dim3(N / 128, 1, lc), kThreads, 0, s>>>(g, xp, wp, w_stride, a,
+                                                                         qp, l0);
+      break;
+    case QkvPick::kTiles: {
+      const int ty = (M + pick.rows - 1) / pick.rows;
+      const bool one = ty == 1;
+      auto kernel = pick.rows == 128   ? (one ? k_qkv_dl<128, 4, 3, 3, false, true>
+                                              : k_qkv_dl<128, 4, 3, 3, false, false>)
+                    : pick.rows == 192 ? (one ? k_qkv_dl<192, 4, 3, 2, false, true>
+                                              : k_qkv_dl<192, 4, 3, 2, false, false>)
+                    : pick.stages == 2 ? k_qkv_dl<256, 2, 2, 2, true, false>
+                    : one              ? k_qkv_dl<256, 2, 3, 2, false, true>
+                                       : k_qkv_dl<256, 2, 3, 2, false, false>;
+      kernel<<<dim3(N / 256, ty, lc), kDlThreads, 0, s>>>(g, xp, wp, w_stride, a, qp, l0);
+      break;
     }
   }
   return hipGetLastError();
