@@ -43,6 +43,8 @@ k_alloc(DevHeader* hdr, int32_t* ring, int32_t* rc, int32_t* tables, int32_t max
   static_assert(KV_MAX_BATCH <= 64, "a lane per request");
   __shared__ int ok;
   __shared__ int64_t s_pos[KV_MAX_BATCH];  // first ring position after the request's copy-on-write
+  __shared__ int32_t s_left[KV_MAX_BATCH];  // tail that the request's copy-on-write left, or -1
+  __shared__ int any_cow;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool req = tid < a.n_req;
   if (wave == 0) {
@@ -55,8 +57,13 @@ k_alloc(DevHeader* hdr, int32_t* ring, int32_t* rc, int32_t* tables, int32_t max
       if (lane >= d) sum += t;
     }
     const int64_t need = __shfl((long long)sum, 63);
-    if (req) s_pos[lane] = head + sum - own + cow;
+    if (req) {
+      s_pos[lane] = head + sum - own + cow;
+      s_left[lane] = -1;
+    }
+    const bool some = __ballot(cow) != 0;
     if (lane == 0) {
+      any_cow = some;
       ok = hdr->status == 0 && hdr->head == head && hdr->tail - head >= need;
       if (ok) hdr->head = head + need;
     }
@@ -71,16 +78,21 @@ k_alloc(DevHeader* hdr, int32_t* ring, int32_t* rc, int32_t* tables, int32_t max
     if (atomicSub(&rc[old], 1) <= 1) hdr->status = KV_ERR_INTERNAL;
     rc[nb] = 1;
     *tail = nb;
+    s_left[tid] = old;
     cow_pairs[tid] = make_int2(old, nb);
   }
   __threadfence_block();
   __syncthreads();
   // the host appends into a partial tail it holds alone; another table
-  // referencing it would see the append's tokens
-  if (req && a.req[tid].cow <= 0 && a.req[tid].partial > 0 &&
-      __hip_atomic_load(&rc[tables[(int64_t)a.req[tid].slot * max_blocks + a.req[tid].first - 1]],
-                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 1)
-    hdr->status = KV_ERR_INTERNAL;
+  // referencing it would see the append's tokens.  Copies that leave it later in
+  // the order of requests do not count.
+  if (req && a.req[tid].cow <= 0 && a.req[tid].partial > 0) {
+    const int32_t t = tables[(int64_t)a.req[tid].slot * max_blocks + a.req[tid].first - 1];
+    int n = __hip_atomic_load(&rc[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (any_cow)
+      for (int r = tid + 1; r < a.n_req; ++r) n += s_left[r] == t;
+    if (n != 1) hdr->status = KV_ERR_INTERNAL;
+  }
   for (int r = wave; r < a.n_req; r += kAllocThreads / 64) {
     int32_t* trow = tables + (int64_t)a.req[r].slot * max_blocks + a.req[r].first;
     for (int i = lane; i < a.req[r].count; i += 64) {
