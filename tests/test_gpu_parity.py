@@ -309,12 +309,12 @@ def test_buffer_checks_before_any_launch(gpu_available):
 
 def test_bf16_fanout_decode_sixteen_agents(gpu_available):
     """16 agents x 4 query heads share a context: 64 query vectors per KV head in
-    the shared chunks, private tails per agent, chunk boundaries crossed."""
+    the shared units, private tails per agent, block boundaries crossed."""
     base = synth.LLAMA8B_SHAPE
     shape = synth.ModelShape("8b-l2", 2, base.d_model, base.n_q_heads, base.n_kv_heads,
                              base.head_dim, base.block_size, "bf16")
     tw = Twin(shape, n_blocks=200, max_pos=1200, max_states=24, wl="fan16", check_kv=False)
-    root = tw.materialize(1030)                    # chunks of 1024 keys: 2 chunks
+    root = tw.materialize(1030)                    # a ragged shared tail
     kids = tw.fork(root, 16)
     tw.attend(kids, 7)                             # copy-on-write of the shared tail
     for _ in range(2):
@@ -355,12 +355,12 @@ def test_bf16_ragged_edges(gpu_available):
 
 
 def test_bf16_decode_batch_one_multichunk(gpu_available):
-    """A batch of one decodes over its keys in 512-key chunks (forked batches
-    use 1024): decode steps over 1030 and 1031 keys span three chunks, the
-    last one ragged, so the split-key partials and their merge are compared
-    with the oracle element by element; a batch of two over the same state
-    and a fork of it takes the 1024-key chunking, then appends 3 tokens each
-    (6 token rows: the decode-size projection with rows of two sequences)."""
+    """A batch of one decodes over its keys in chunks of its own (here 256 keys:
+    decode steps over 1030 and 1031 keys span five, the last one ragged), so the
+    split-key partials and their merge are compared with the oracle element by
+    element; a batch of two over the same state and a fork of it is cut
+    otherwise, then appends 3 tokens each (6 token rows: the decode-size
+    projection with rows of two sequences)."""
     base = synth.LLAMA8B_SHAPE
     shape = synth.ModelShape("8b-l2", 2, base.d_model, base.n_q_heads, base.n_kv_heads,
                              base.head_dim, base.block_size, "bf16")

@@ -9,8 +9,8 @@ oracle's re-rotation of the stored source keys):
 * layer groups: a scratch area smaller than a call needs for all layers, so
   that the call runs layer group by layer group (prefill, append, batched
   decode with its work plan reused across groups);
-* decode batches beyond 64 query vectors per KV head (four wavefronts per
-  unit, query slices) and contexts of more than 256 key chunks;
+* decode batches beyond 64 query vectors per KV head (four or eight wavefronts
+  per unit, query slices) and contexts of more than 256 lists of units;
 * a Llama-scale RoPE base (5e5) at positions near 35k and compositions that
   shift segments by about +-30k positions;
 * the projection kernels for d_model values and row counts the 8B / 70B
@@ -137,7 +137,8 @@ def test_decode_query_slices(gpu_available):
     MFMA decode path (the merge kernel runs): 32 agents x 4 query heads at
     the 8B head shape (128 vectors: four wavefronts of 32 share a unit's
     stages), 64 agents x 4 query heads and 17 agents x 8 query heads at the
-    70B head shape (more than 128: query slices of 64 vectors)."""
+    70B head shape (up to 256: eight wavefronts), 41 agents x 8 query heads
+    (328: six query slices of up to 64 vectors)."""
     shape = shape8b(L=2)
     tw = Twin(shape, n_blocks=260, max_pos=1200, max_states=70, wl="slices", check_kv=False)
     hdr, ohdr, buf, pay = tw.synthetic_transfer(66, 1050, 0, tag=2)   # 1050 keys: 2 chunks
@@ -157,13 +158,16 @@ def test_decode_query_slices(gpu_available):
     base = synth.LLAMA70B_SHAPE
     shape = synth.ModelShape("70b-l2", 2, base.d_model, base.n_q_heads, base.n_kv_heads,
                              base.head_dim, base.block_size, "bf16")
-    tw = Twin(shape, n_blocks=80, max_pos=512, max_states=20, wl="slices70", check_kv=False)
+    tw = Twin(shape, n_blocks=100, max_pos=512, max_states=44, wl="slices70", check_kv=False)
     root = tw.materialize(300)
     kids = tw.fork(root, 17)
     kv.kv_profile_enable(tw.gpu.h, True)
     tw.attend(kids, 1)
     tw.attend(kids, 1)
-    assert kv.kv_profile_read(tw.gpu.h)["merge"][0] == 2
+    more = tw.fork(root, 24)
+    tw.attend(kids + more, 1)
+    tw.attend(kids + more, 1)
+    assert kv.kv_profile_read(tw.gpu.h)["merge"][0] == 4
     tw.close()
 
 
@@ -240,8 +244,8 @@ def test_decode_many_chunks(gpu_available):
               check_kv=False)
     hdr, ohdr, buf, pay = tw.synthetic_transfer(nb, n_ctx, 0, tag=3)
     root = tw.unpack(hdr, ohdr, buf, pay)
-    tw.attend([root], 1)                    # 139991 keys, batch 1: 274 chunks
+    tw.attend([root], 1)                    # 139991 keys, batch 1
     kids = tw.fork(root, 3)
-    tw.attend(kids[:2], 1)                  # batch 2: 137 chunks
+    tw.attend(kids[:2], 1)                  # batch 2
     tw.attend(kids, 1)                      # mixed histories, batch 3
     tw.close()

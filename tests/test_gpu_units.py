@@ -8,6 +8,8 @@ fork of a fork inside one chunk, members whose histories share nothing, key
 counts that end one key into a block, and units on both sides of the 32 query
 vectors that separate the two kernels.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -110,6 +112,54 @@ def test_packed_appends_that_share_little(gpu_available, hq, T):
     short = tw.fork(roots[1], 4)
     tw.attend(short, 130)                            # 130 private keys after 63 common ones
     tw.attend(short + forks, T)
+    tw.close()
+
+
+def area_for(cfg, agents, T, keys, groups):
+    """The largest work area in which the call takes its wide form in layer
+    groups of `groups` layers (asked of the library), and the form's path."""
+    out = (ctypes.c_int64 * 8)()
+    f = kv.lib().kvs_query_append
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
+                  ctypes.c_size_t, ctypes.c_void_p]
+    lo, hi, found = 0, 1 << 32, None
+    while hi - lo > 256:                       # layers per group grow with the area
+        mid = (lo + hi) // 2
+        assert f(ctypes.byref(cfg), agents, T, keys, mid, out) == 0
+        if out[0] <= groups:
+            lo = mid
+            if out[0] == groups and out[2] == 1:
+                found = (mid, out[3])
+        else:
+            hi = mid
+    return found
+
+
+@pytest.mark.parametrize("L,hq,hkv,n_ctx,agents,T,path", [
+    (4, 4, 1, 2100, 24, 1, 3),                 # split-key decode: units and late masks
+    (4, 8, 1, 2100, 16, 1, 3),
+    (32, 32, 8, 600, 9, 20, 2),                # packed appends: the packs' shared keys
+])
+@pytest.mark.parametrize("part", [1, 3])
+def test_layer_groups_of_the_wide_forms(gpu_available, L, hq, hkv, n_ctx, agents, T, path, part):
+    """What the first layer group works out once serves the later ones: a
+    quarter or three quarters of the layers at once, against the float64
+    oracle."""
+    shape = synth.ModelShape("8b-g", L, 512, hq, hkv, 128, 16, "bf16")
+    groups = part * L // 4
+    cfg = kv.make_cfg(L, 512, hq, hkv, 128, 16, "bf16", n_ctx + 128, agents + 4)
+    area, got = area_for(cfg, agents, T, n_ctx + 2 * T, groups)
+    assert got == path
+    tw = Twin(shape, n_blocks=-(-n_ctx // 16) + agents * 8 + 8, max_pos=n_ctx + 128,
+              max_states=agents + 4, wl="lgw", check_kv=False, scratch_bytes=area)
+    kids = tw.fork(context(tw, n_ctx, 31), agents)
+    kv.kv_profile_enable(tw.gpu.h, True)
+    for i in range(2):
+        tw.attend(kids, T)
+        prof = kv.kv_profile_read(tw.gpu.h)
+        n = -(-L // groups)
+        assert prof["attn_decode" if T == 1 else "attn"][0] == n, prof
+        assert prof["merge"][0] == (n if path == 3 else 0), prof
     tw.close()
 
 
