@@ -675,8 +675,9 @@ bool attn_mfma_ok(const PoolGeom& g, int dtype, const AppendDesc& a) {
 namespace {
 // Sequences per workgroup of the packed form, 1 where it does not apply: as
 // many whole sequences as the workgroup's token groups hold, while every CU
-// (256) still gets a workgroup: with fewer, sequences that share nothing
-// would be slower one after the other than side by side.
+// still gets a workgroup: with fewer, sequences would be slower one after the
+// other than side by side.  (256 CUs as a constant: the work area's size, which
+// is asked for without a device, follows from it.)
 int pack_size(const PoolGeom& g, const AppendDesc& a) {
   const int G = g.Hq / g.Hkv;
   const int64_t fit = 32 * (kPW / G) / a.T;

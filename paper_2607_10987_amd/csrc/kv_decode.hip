@@ -917,7 +917,9 @@ constexpr int kMaxVecAppend = 128;
 // chunk costing its keys, its partials and about 32 keys to start.  (Rounds of
 // the whole call: in a work area that cuts it into layer groups they are
 // smaller.)  A batch of one has no shared blocks and its chunks are its only
-// parallelism: about 512 (+5-10% against 1024).
+// parallelism: about 512 (+5-10% against 1024).  The device's 256 CUs are a
+// constant here: kv_scratch_bytes, which asks no device, has to arrive at the
+// same form as the launch.
 int64_t wide_keys(int64_t batch, int64_t vec) {
   return std::max<int64_t>(batch == 1 ? kCK / 2 : kCK, std::min<int64_t>(16 * vec, 4 * kCK));
 }
