@@ -59,7 +59,8 @@ def spoil(x, agent):
 @pytest.mark.parametrize("L,hq,hkv,n_ctx,agents,T,what", [
     (32, 32, 8, 200, 9, 29, "packed: two agents a workgroup share a wavefront's rows"),
     (32, 32, 8, 130, 9, 32, "packed: a wavefront's rows are of one agent"),
-    (32, 32, 8, 40, 11, 5, "packed: many agents a wavefront, less than a tile shared"),
+    (32, 32, 8, 70, 11, 5, "packed: many agents a wavefront, one tile shared"),
+    (32, 32, 8, 40, 11, 5, "packed launch, a workgroup per agent: less than a tile shared"),
     (32, 64, 8, 130, 8, 11, "packed: eight query heads"),
     (2, 32, 8, 2100, 8, 4, "split-key: appends"),
     (2, 32, 8, 1041, 33, 1, "split-key: decode, shared units and private tails"),

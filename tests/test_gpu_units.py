@@ -75,8 +75,8 @@ def test_nested_forks_and_unrelated_members(gpu_available):
 
 
 @pytest.mark.parametrize("n_ctx,agents,T", [
-    (63, 10, 16),     # less than a tile shared; four sequences a workgroup
-    (64, 11, 16),     # one whole tile shared; a last workgroup of three
+    (63, 10, 16),     # less than a tile shared: a workgroup per sequence
+    (64, 11, 16),     # one whole tile shared by four sequences; a last workgroup of three
     (200, 9, 32),     # two sequences a workgroup, a whole token group each
     (1000, 21, 3),    # 21 sequences of 3 tokens in one workgroup
     (130, 33, 2),     # the most sequences per workgroup, and one left over
