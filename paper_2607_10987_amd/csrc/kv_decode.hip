@@ -972,6 +972,7 @@ DecodeForm decode_form(const PoolGeom& g, const AppendDesc& a, bool wide) {
         best = rate;
         ck = c;
       }
+      n = nch;  // down to here the chunk is the same
     }
     f.ck = one && !few && kilo < 4 ? 384 : (int)ck;
   }
@@ -1041,7 +1042,7 @@ void decode_query(const PoolGeom& g, const AppendDesc& a, bool wide, int64_t* ou
 // max_keys keys takes.  The smallest layout has a formula; the wide form is
 // asked for each (batch, T): its choice only changes where a multiple of 64 keys
 // or a half step of wide_chunks is passed, so both ends of every 64 keys cover
-// all key counts.  A few ms; the formula with the most chunks that decode_form
+// all key counts.  Some ms; the formula with the most chunks that decode_form
 // considers is twice as much scratch (8B shape, 16 agents, 33792 keys: 866 MB
 // against 416; the smallest layout takes 285).
 size_t decode_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int64_t batch,
