@@ -147,8 +147,8 @@ kv_status kv_pool_bytes(const kv_model_cfg* cfg, int64_t n_blocks, size_t* pool_
  * that takes less (agents share the keys of whole 1024-key chunks only, about
  * two thirds of the bytes), and layers are processed in groups (at least one
  * layer must fit).  Which form ran may show in the last bits of an output
- * (sums end at other keys).  Host arithmetic, some ms (a tenth of a
- * second for contexts of 100000s of keys). */
+ * (sums end at other keys).  Host arithmetic, about a ms (some tens
+ * for contexts of 100000s of keys). */
 size_t kv_scratch_bytes(const kv_model_cfg* cfg, int64_t tokens, int32_t batch,
                         int64_t max_keys);
 

@@ -1040,11 +1040,14 @@ void decode_query(const PoolGeom& g, const AppendDesc& a, bool wide, int64_t* ou
 
 // The most that any call of up to `batch` states, `tokens` new tokens in all and
 // max_keys keys takes.  The smallest layout has a formula; the wide form is
-// asked for each (batch, T): its choice only changes where a multiple of 64 keys
-// or a half step of wide_chunks is passed, so both ends of every 64 keys cover
-// all key counts.  Some ms; the formula with the most chunks that decode_form
-// considers is twice as much scratch (8B shape, 16 agents, 33792 keys: 866 MB
-// against 416; the smallest layout takes 285).
+// asked for each number of rows, of one state and of several (how many only
+// matters for the plan's LDS, far above the chunks of appends).  Its choice
+// only changes where a multiple of 64 keys or a half step of wide_chunks is
+// passed, so both ends of every 64 keys cover all key counts, from the most
+// down to where a formula with the most chunks that it considers is no more
+// than what was found.  That formula alone would ask for twice as much (8B
+// shape, 16 agents, 33792 keys: 866 MB against 416; the smallest layout takes
+// 285).
 size_t decode_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int64_t batch,
                             int64_t max_keys) {
   const int64_t L = g.L, Hq = g.Hq, G = g.Hq / g.Hkv;
@@ -1062,28 +1065,32 @@ size_t decode_scratch_bound(const PoolGeom& g, int dtype, int64_t tokens, int64_
     a.T = (int32_t)T;
     const int64_t want = wide_keys(b, b * T * G);
     for (int64_t hi = (max_keys + 63) / 64 * 64; hi > 0; hi -= 64) {
-      const int64_t n = 2 * wide_chunks(hi, want) + 1;  // at least as many as decode_form takes
+      const int64_t n0 = wide_chunks(hi, want), n = b * T == 1 ? 2 * n0 : n0 + (n0 + 1) / 2;
       if (total(b * T, b, b > 1 ? 2 * n : n, 3 * want) <= worst) return;
-      const int64_t at[2] = {std::max(T, hi - 63), std::min(max_keys, hi)};
-      if (at[0] > at[1]) continue;
-      bool any = false;
-      for (const int64_t keys : at) {
+      for (const int64_t keys : {std::max(T, hi - 63), std::min(max_keys, hi)}) {
+        if (keys < T || keys > max_keys) continue;
         a.max_keys = (int32_t)keys;
-        any |= decode_mfma_ok(g, dtype, a);
-      }
-      for (const int64_t keys : at) {
-        if (!any) break;
-        a.max_keys = (int32_t)keys;
+        if (T > 1 && !attn_mfma_ok(g, dtype, a)) continue;  // too long a block table
         size_t per = 0, fixed = 0;
         decode_scratch(g, a, true, &per, &fixed);
         worst = std::max(worst, L * per + fixed);
       }
     }
   };
+  a.batch = a.T = a.max_keys = 1;
+  if (!decode_mfma_ok(g, dtype, a)) return worst;
+  const bool appends = attn_mfma_ok(g, dtype, a);
   const int64_t most = std::min<int64_t>(batch, KV_MAX_BATCH);
   for (int64_t b = most; b >= 1; --b) wide(b, 1);
-  for (int64_t b = 1; b <= most; ++b)
-    for (int64_t T = std::min(tokens, (int64_t)kMaxVecAppend / G) / b; T > 1; --T) wide(b, T);
+  const int64_t rows = appends ? std::min(tokens, (int64_t)kMaxVecAppend / G) : 0;
+  for (int64_t r = rows; r > 1; --r) {
+    wide(1, r);
+    for (int64_t b = 2; r > most && b <= most; ++b)  // r <= most: as r states of a token
+      if (r % b == 0) {
+        wide(b, r / b);
+        break;
+      }
+  }
   return worst;
 }
 
